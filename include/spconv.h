@@ -213,6 +213,11 @@ size_t spconv_forward_workspace_bytes(const spconv_map* m, int c_in, int c_out, 
  * Requirements: c_in, c_out in [1, 1024]; 16-byte rows (c * element size % 16 == 0)
  * and c_out % 16 == 0; d_x, d_w, d_y (and d_residual) 16-byte aligned, else
  * SPCONV_EINVAL.  Asynchronous on `stream`; no host synchronisation.
+ * Narrow layers, whose K^3 weight matrices fit the LDS of a CU, run as one kernel that
+ * sums every offset's products in float32 and never forms GEMM partials, unless an option
+ * names a form of the separate steps (gather, centre, partial_dtype, t_gather or
+ * t_scatter given) or d_y overlaps d_x or d_w; grouping and gemm_tile_rows have nothing
+ * to shape there.
  * A SPCONV_SUBM map with odd K builds the input-side metadata table of Algorithm
  * 1's gather lazily: the first call that gathers through the table (gather =
  * SPCONV_GATHER_BUFFER) fills it from the pair lists on its `stream`, so calls on
@@ -258,7 +263,8 @@ int spconv_concat_rows(const void* d_a, int c_a, const void* d_b, int c_b, void*
 
 /* What spconv_forward will launch for this map (host-only): padded and real
  * buffer rows (padding overhead = (padded - real) / real, Section 3 figure on
- * GEMM reordering), number of GEMM launches, the tiles used and the gather form. */
+ * GEMM reordering), number of GEMM launches, the tiles used and the gather form.  For
+ * a narrow layer that runs as one kernel: what the separate steps would launch. */
 typedef struct {
   int64_t rows_real;
   int64_t rows_padded;

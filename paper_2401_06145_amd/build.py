@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libspconv.so")
-SOURCES = ["api.hip", "scan.hip", "map_kernels.hip", "gmas_kernels.hip", "gemm_mfma.hip"]
+SOURCES = ["api.hip", "scan.hip", "map_kernels.hip", "gmas_kernels.hip", "gemm_mfma.hip", "conv_small.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

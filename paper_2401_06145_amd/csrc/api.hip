@@ -90,7 +90,7 @@ const char* prof_name(int id) {
       "scatter", "hash", "", "", "", "",
       "k_minmax", "k_radix_hist", "k_radix_scatter", "k_scan", "k_copy", "k_down_keys", "k_unique", "k_backward",
       "k_forward_count", "k_forward_write", "k_fill", "k_radix_local", "k_gather", "k_gemm", "k_scatter", "k_pack",
-      "k_hash_insert", "k_hash_probe", "k_scatter_centre", "", "", "", "", ""};
+      "k_hash_insert", "k_hash_probe", "k_scatter_centre", "k_conv_small", "", "", "", ""};
   return (id >= 0 && id < PROF_IDS) ? kNames[id] : "";
 }
 struct PhaseRec {
@@ -511,6 +511,22 @@ size_t plan_forward_ws(void* base, const spconv_map* m, int c_in, int c_out, con
   // (rows are pair indices: with the centre fused its rows stay unused)
   b->buf_out = a.take_bytes((size_t)(p.rows_pairs + 1) * c_out * p.pelem);
   return align_up(a.off, 256);
+}
+
+// Whether a call runs as the one-kernel form (conv_small.hip).  Grouping and GEMM tile
+// rows only shape launches of the separate steps, and do not rule it out.
+bool one_kernel(const spconv_map* m, const void* x, const void* w, const void* y, int c_in, int c_out,
+                const GmasPlan& p, const spconv_options* opt) {
+  // options that name a form of the separate steps keep them
+  if (opt && (opt->centre || opt->gather || opt->partial_dtype || opt->t_gather || opt->t_scatter)) return false;
+  if (p.rows_pairs == 0 || !m->omt || !conv_small_applies(m->n_in, m->n_out, m->K3, c_in, c_out, p.dtype)) return false;
+  // outputs are written while other workgroups still read inputs and weights
+  auto apart = [](const void* a, int64_t na, const void* b, int64_t nb) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa + (uintptr_t)na <= pb || pb + (uintptr_t)nb <= pa;
+  };
+  const int64_t yb = m->n_out * c_out * p.elem;
+  return apart(x, m->n_in * c_in * p.elem, y, yb) && apart(w, (int64_t)m->K3 * c_in * c_out * p.elem, y, yb);
 }
 
 }  // namespace
@@ -957,6 +973,14 @@ int forward_impl(const spconv_map* m, const void* d_x, const void* d_w, void* d_
   plan_forward_ws(d_workspace, m, c_in, c_out, p, &b);
   if (m->n_out == 0) return SPCONV_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (one_kernel(m, d_x, d_w, d_y, c_in, c_out, p, opt)) {
+    PhaseScope ph(PH_GEMM, s);
+    const bool stream = m->n_out * c_out * p.elem >= kStreamOutputBytes;
+    SPC_TRY(launch_conv_small(d_x, m->n_in, d_w, m->pin, m->omt, m->omt_stride, m->out_perm, m->K3, d_y, d_residual,
+                              relu, m->n_out, c_in, c_out, dtype, stream, s),
+            "one-kernel convolution");
+    return SPCONV_OK;
+  }
   // a map without tables has no pairs: the scatter then writes zeros (plus the epilogue)
   const int K3 = m->omt ? m->K3 : 0;
   if (p.rows_pairs > 0) {

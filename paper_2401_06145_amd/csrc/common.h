@@ -106,7 +106,7 @@ enum ProfId : int {
   // kernels
   KN_MINMAX = 16, KN_RADIX_HIST, KN_RADIX_SCATTER, KN_SCAN, KN_COPY, KN_DOWN_KEYS, KN_UNIQUE,
   KN_BACKWARD, KN_FORWARD_COUNT, KN_FORWARD_WRITE, KN_FILL, KN_RADIX_LOCAL, KN_GATHER, KN_GEMM, KN_SCATTER,
-  KN_PACK, KN_HASH_INSERT, KN_HASH_PROBE, KN_SCATTER_CENTRE,
+  KN_PACK, KN_HASH_INSERT, KN_HASH_PROBE, KN_SCATTER_CENTRE, KN_CONV_SMALL,
   PROF_IDS = 40
 };
 struct ProfScope {
@@ -289,5 +289,12 @@ hipError_t launch_scatter_centre(const void* x, const uint32_t* perm, const void
                                  const void* buf_out, const int32_t* omt, int64_t mt_stride, int K3, void* y,
                                  const void* residual, int relu, int64_t n_out, int c_in, int c_out, int dtype,
                                  int part_dtype, bool stream, hipStream_t s);
+
+// conv_small.hip: the whole GMaS step of a narrow layer in one kernel, without partial
+// rows.  Whether an instance serves the layer, and the launcher.
+bool conv_small_applies(int64_t n_in, int64_t n_out, int K3, int c_in, int c_out, int dtype);
+hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
+                             int64_t mt_stride, const uint32_t* perm, int K3, void* y, const void* residual, int relu,
+                             int64_t n_out, int c_in, int c_out, int dtype, bool stream, hipStream_t s);
 
 }  // namespace spc
