@@ -502,7 +502,7 @@ struct FwdBufs {
 
 size_t plan_forward_ws(void* base, const spconv_map* m, int c_in, int c_out, const GmasPlan& p, FwdBufs* b) {
   Bump a(base);
-  b->wt = (gemm_wide(c_in, c_out, p.dtype, p.part_dtype) && gemm_wide_transposed(c_in, c_out))
+  b->wt = (gemm_wide(c_in, c_out, p.dtype, p.part_dtype) && gemm_wide_transposed(c_in, c_out, p.dtype))
               ? a.take_bytes((size_t)m->K3 * c_in * c_out * p.elem)
               : nullptr;
   // the fused gather reads the input rows directly: no gathered buffer

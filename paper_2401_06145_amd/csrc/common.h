@@ -265,7 +265,7 @@ struct GemmSeg {
 // Whether the full-width kernel applies, and whether it wants the weights
 // transposed beforehand (large W_k; small ones are transposed while staging).
 bool gemm_wide(int c_in, int c_out, int dtype, int part_dtype);
-bool gemm_wide_transposed(int c_in, int c_out);
+bool gemm_wide_transposed(int c_in, int c_out, int dtype);
 // wt[k][n][c] = w[k][c][n] for 16-bit weights.
 hipError_t launch_transpose_w(const void* w, void* wt, int K3, int c_in, int c_out, hipStream_t s);
 // Launches the segments (any number; split into launches of at most 64 segments).

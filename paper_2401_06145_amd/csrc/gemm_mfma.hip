@@ -21,12 +21,17 @@
 // layer's input features themselves: row r is then input row a_rows[r], the input
 // index of pair r.  The fused form never writes or reads the gathered buffer.
 //
-// Two kernels.  k_gemm_wide (f16 / bf16, c_in <= 512) gives a workgroup the full
-// output width whenever W_k^T fits the 160 KiB of LDS, so every buf_in row is
-// read from HBM once; it stages W_k^T from a transposed copy of the weights
-// with 16-byte copies, and each wave loads the next 16-row block of buf_in while
-// it multiplies the current one.  k_gemm is the general fallback (any c_in,
-// float32) with a narrower column slice per workgroup.
+// Two kernels.  k_gemm_wide (f16 / bf16 with c_in <= 512, float32 with c_in <= 256)
+// gives a workgroup the full output width whenever W_k^T fits the 160 KiB of LDS, so
+// every buf_in row is read from HBM once; it stages W_k^T from a transposed copy of the
+// weights with 16-byte copies (float32: from W itself, 4 x 4 pieces transposed in
+// registers), and each wave loads the next 16-row block of buf_in while it multiplies
+// the current one.  k_gemm is the general fallback (any c_in) with a narrower column
+// slice per workgroup.  float32 is bound by the rows it moves up to about 96 channels
+// and by v_mfma_f32_16x16x4_f32 from 128 on; its loads of 4 channels per lane and k-step
+// in k_gemm made four times the load instructions.  Layers through k_gemm and
+// k_gemm_wide: 120k LiDAR 64 -> 64, 92 -> 70 us; 256 -> 256, 1526 -> 567 us; 100k indoor
+// 128 -> 128, 306 -> 171 us; 37k LiDAR level-1 128 -> 256, 412 -> 217 us.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -90,6 +95,24 @@ struct Mfma<float> {
   __device__ static frag load(const float* p) { return *p; }
   __device__ static frag zero() { return 0.f; }
   __device__ static f32x4 mma(frag a, frag b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+
+// The full-width kernel's view: 16-byte fragments.  float32: four products of 4
+// channels; product j takes channel j of every lane's four, for both operands alike, so
+// together they cover the k-step's 16 channels.
+template <typename T>
+struct MfmaWide : Mfma<T> {};
+template <>
+struct MfmaWide<float> {
+  static constexpr int KS = 16;
+  static constexpr int KSUB = 4;
+  using frag = f32x4;
+  __device__ static frag load(const float* p) { return *reinterpret_cast<const frag*>(p); }
+  __device__ static f32x4 mma(frag a, frag b, f32x4 c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+  }
 };
 
 template <typename T>
@@ -172,8 +195,9 @@ constexpr size_t kLdsMax = 160 * 1024;
 // bytes, each row padded by 16 bytes.
 constexpr int kStageRow = 128 + 16;
 constexpr size_t kStageBytes = (size_t)kWideWaves * 16 * kStageRow;
-// LDS of one full-width workgroup: the W_k^T slice plus the store stages.
-constexpr size_t wide_lds(int nt, int ldk) { return (size_t)16 * nt * ldk * 2 + kStageBytes; }
+// LDS of one full-width workgroup: the W_k^T slice (rows of ks 64-byte k-steps and 16
+// bytes of padding) plus the store stages.
+constexpr size_t wide_lds(int nt, int ks) { return (size_t)16 * nt * (64 * ks + 16) + kStageBytes; }
 
 // Register blocking of the full-width kernel.  A wave computes MB 16-row blocks
 // times NTW 16-column tiles, so every W^T fragment it reads from LDS feeds MB
@@ -214,9 +238,11 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
                                                             TO* __restrict__ C,
                                                             TO* __restrict__ dump, int c_in, int c_out, int ldk,
                                                             int rows_per_tile, int nsl, int stream) {
-  using M = Mfma<T>;
+  using M = MfmaWide<T>;
   using F = typename M::frag;
-  static_assert(M::KS == 32, "16-bit operands only");
+  constexpr int KS = M::KS;      // channels per k-step
+  constexpr int E = M::KSUB;     // channels per 16-byte fragment or chunk
+  static_assert(E * sizeof(T) == 16 && KS == 4 * E, "16-byte fragments");
   constexpr int CG = wide_cg(NT);
   constexpr int NTW = NT / CG;
   constexpr int MB = wide_mb(NTW, KSTEPS);
@@ -229,7 +255,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   extern __shared__ __align__(16) unsigned char smem[];
   T* lw = reinterpret_cast<T*>(smem);  // [BN][ldk], W_k^T slice
   constexpr int BN = 16 * NT;
-  constexpr int KP = 32 * KSTEPS;
+  constexpr int KP = KS * KSTEPS;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = tid / kWave;
@@ -261,7 +287,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   const int sub = lane >> 4;
   const int col = lane & 15;
   const int nw = 16 * NTW * cg;  // this wave's first column within the slice
-  const T* lwp = lw + (nw + col) * ldk + 8 * sub;
+  const T* lwp = lw + (nw + col) * ldk + E * sub;
   // store stage: GC tiles per segment (128 bytes, or fewer tiles when the chunk's
   // tile count is not a multiple), SLANES lanes of 16 bytes per row, SROWS rows
   // per read, SREADS reads for the 16 rows
@@ -294,65 +320,114 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
       const T* arow = A + r * (int64_t)c_in;
 #pragma unroll
       for (int q = 0; q < KSTEPS; ++q) {
-        const int kk = 32 * q + 8 * sub;
+        const int kk = KS * q + E * sub;
         raw[b][q] = M::load((row < row_lim && kk < c_in) ? arow + kk : A);
       }
     }
   };
 
   // Prologue, ordered so that its round trips overlap: the first blocks' source
-  // rows, then the first kWStage 16-byte chunks of the W_k^T slice per thread, then
-  // the first blocks' operands (they wait only for their rows), then the chunks go
-  // to LDS.  A chunk is 8 consecutive k of one column n when read from the
-  // transposed copy, or 8 consecutive n of one k when read from W itself (and
-  // transposed on the way into LDS).  k past c_in is zero.
+  // rows, then the first pieces of the W_k^T slice, then the first blocks' operands
+  // (they wait only for their rows), then the pieces go to LDS.  k past c_in is zero.
   const int m_first = r_begin + rg * MB * 16;
   fetch_rows(m_first);
-  constexpr int CH_T = KP / 8;  // chunks per W^T row (transposed copy)
-  constexpr int CH_N = BN / 8;  // chunks per W row slice (plain copy)
-  constexpr int NCHUNK = BN * KP / 8;
-  const T* wk_t = wt ? wt + ((int64_t)k * c_out + n0) * c_in : nullptr;
-  const T* wk_p = w + (int64_t)k * c_in * c_out + n0;
-  auto chunk_nc = [&](int idx, int* n, int* c) {
-    if (wt) {
-      *n = idx / CH_T;
-      *c = (idx - *n * CH_T) * 8;
-    } else {
-      *c = idx / CH_N;
-      *n = (idx - *c * CH_N) * 8;
+  if (wt) {
+    // from the transposed copy: 16-byte chunks, kWStage per thread in flight at a time
+    constexpr int CH_T = KP / E;  // chunks per W^T row
+    constexpr int NCHUNK = BN * KP / E;
+    constexpr int kWStage = 8;
+    const T* wk_t = wt + ((int64_t)k * c_out + n0) * c_in;
+    uint4 wv[kWStage];
+    auto load_chunks = [&](int cb) {
+#pragma unroll
+      for (int u = 0; u < kWStage; ++u) {
+        const int idx = cb + u * kWideThreads + tid;
+        const int n = idx / CH_T, c = (idx - n * CH_T) * E;
+        wv[u] = (idx < NCHUNK && c < c_in) ? *reinterpret_cast<const uint4*>(wk_t + (int64_t)n * c_in + c)
+                                           : make_uint4(0, 0, 0, 0);
+      }
+    };
+    auto store_chunks = [&](int cb) {
+#pragma unroll
+      for (int u = 0; u < kWStage; ++u) {
+        const int idx = cb + u * kWideThreads + tid;
+        const int n = idx / CH_T, c = (idx - n * CH_T) * E;
+        if (idx < NCHUNK) *reinterpret_cast<uint4*>(lw + n * ldk + c) = wv[u];
+      }
+    };
+    load_chunks(0);
+    issue(m_first);
+    store_chunks(0);
+    for (int cb = kWStage * kWideThreads; cb < NCHUNK; cb += kWStage * kWideThreads) {
+      load_chunks(cb);
+      store_chunks(cb);
     }
-  };
-  auto load_chunk = [&](int idx) -> uint4 {
-    int n, c;
-    chunk_nc(idx, &n, &c);
-    if (idx >= NCHUNK || c >= c_in) return make_uint4(0, 0, 0, 0);
-    return wt ? *reinterpret_cast<const uint4*>(wk_t + (int64_t)n * c_in + c)
-              : *reinterpret_cast<const uint4*>(wk_p + (int64_t)c * c_out + n);
-  };
-  auto store_chunk = [&](int idx, const uint4& v) {
-    if (idx >= NCHUNK) return;
-    int n, c;
-    chunk_nc(idx, &n, &c);
-    if (wt) {
-      *reinterpret_cast<uint4*>(lw + n * ldk + c) = v;
-    } else {
-      const T* e = reinterpret_cast<const T*>(&v);
+  } else if constexpr (E == 8) {
+    // from W itself, transposed on the way into LDS: a chunk is 8 consecutive n of one k
+    constexpr int CH_N = BN / 8;  // chunks per W row slice
+    constexpr int NCHUNK = KP * CH_N;
+    constexpr int kWStage = 8;
+    const T* wk_p = w + (int64_t)k * c_in * c_out + n0;
+    uint4 wv[kWStage];
+    auto load_chunks = [&](int cb) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) lw[(n + j) * ldk + c] = e[j];
+      for (int u = 0; u < kWStage; ++u) {
+        const int idx = cb + u * kWideThreads + tid;
+        const int c = idx / CH_N, n = (idx - c * CH_N) * 8;
+        wv[u] = (idx < NCHUNK && c < c_in) ? *reinterpret_cast<const uint4*>(wk_p + (int64_t)c * c_out + n)
+                                           : make_uint4(0, 0, 0, 0);
+      }
+    };
+    auto store_chunks = [&](int cb) {
+#pragma unroll
+      for (int u = 0; u < kWStage; ++u) {
+        const int idx = cb + u * kWideThreads + tid;
+        const int c = idx / CH_N, n = (idx - c * CH_N) * 8;
+        const T* e = reinterpret_cast<const T*>(&wv[u]);
+        if (idx < NCHUNK) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) lw[(n + j) * ldk + c] = e[j];
+        }
+      }
+    };
+    load_chunks(0);
+    issue(m_first);
+    store_chunks(0);
+    for (int cb = kWStage * kWideThreads; cb < NCHUNK; cb += kWStage * kWideThreads) {
+      load_chunks(cb);
+      store_chunks(cb);
     }
-  };
-  constexpr int kWStage = 8;  // chunks per thread in flight at a time
-  uint4 wv[kWStage];
+  } else {
+    // float32, from W itself: 4 x 4 pieces, 16-byte accesses both ways
+    constexpr int PC = KP / E;  // pieces along k
+    constexpr int NPIECE = PC * (BN / E);
+    const T* wk_p = w + (int64_t)k * c_in * c_out + n0;
+    uint4 in[E];
+    auto load_piece = [&](int idx) {
+      const int n = idx / PC * E, c = (idx - idx / PC * PC) * E;
 #pragma unroll
-  for (int u = 0; u < kWStage; ++u) wv[u] = load_chunk(u * kWideThreads + tid);
-  issue(m_first);
+      for (int j = 0; j < E; ++j)
+        in[j] = (idx < NPIECE && c < c_in) ? *reinterpret_cast<const uint4*>(wk_p + (int64_t)(c + j) * c_out + n)
+                                           : make_uint4(0, 0, 0, 0);
+    };
+    auto store_piece = [&](int idx) {
+      if (idx >= NPIECE) return;
+      const int n = idx / PC * E, c = (idx - idx / PC * PC) * E;
 #pragma unroll
-  for (int u = 0; u < kWStage; ++u) store_chunk(u * kWideThreads + tid, wv[u]);
-  for (int cb = kWStage * kWideThreads; cb < NCHUNK; cb += kWStage * kWideThreads) {
+      for (int m = 0; m < E; ++m) {
+        T out[E];
 #pragma unroll
-    for (int u = 0; u < kWStage; ++u) wv[u] = load_chunk(cb + u * kWideThreads + tid);
-#pragma unroll
-    for (int u = 0; u < kWStage; ++u) store_chunk(cb + u * kWideThreads + tid, wv[u]);
+        for (int j = 0; j < E; ++j) out[j] = reinterpret_cast<const T*>(&in[j])[m];
+        *reinterpret_cast<uint4*>(lw + (n + m) * ldk + c) = *reinterpret_cast<const uint4*>(out);
+      }
+    };
+    load_piece(tid);
+    issue(m_first);
+    store_piece(tid);
+    for (int idx = tid + kWideThreads; idx < NPIECE + tid; idx += kWideThreads) {
+      load_piece(idx);
+      store_piece(idx);
+    }
   }
   __syncthreads();
 
@@ -364,7 +439,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   uint32_t kmask[KSTEPS];
 #pragma unroll
   for (int q = 0; q < KSTEPS; ++q) {
-    uint32_t m = (32 * q + 8 * sub < c_in) ? 0xFFFFFFFFu : 0u;
+    uint32_t m = (KS * q + E * sub < c_in) ? 0xFFFFFFFFu : 0u;
     asm("" : "+v"(m));
     kmask[q] = m;
   }
@@ -411,7 +486,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
         if constexpr (MB > 1) asm volatile("" ::: "memory");
         F wf[NTC];
 #pragma unroll
-        for (int t = 0; t < NTC; ++t) wf[t] = M::load(lwp + 16 * (ch * NTC + t) * ldk + 32 * q);
+        for (int t = 0; t < NTC; ++t) wf[t] = M::load(lwp + 16 * (ch * NTC + t) * ldk + KS * q);
 #pragma unroll
         for (int t = 0; t < NTC; ++t)
 #pragma unroll
@@ -878,27 +953,28 @@ const void* centre_kernel_for(int dtype, int part_dtype, int nt, int ks) {
   return nullptr;
 }
 
-// k-steps instantiated for the wide kernel (c_in up to 512); others round up
-int wide_ksteps(int c_in) {
-  const int ks = (c_in + 31) / 32;
+// k-steps instantiated for the wide kernel (c_in up to 512, float32 256); others round up
+int wide_ksteps(int c_in, int elem) {
+  const int ks = (c_in * elem + 63) / 64;
   for (int c : {1, 2, 3, 4, 6, 8, 12, 16})
     if (ks <= c) return c;
   return 0;
 }
 
 // Instantiated (NT, KSTEPS) pairs: the W^T slice fits the LDS.
-constexpr bool wide_fits(int nt, int ks) { return wide_lds(nt, 32 * ks + 8) <= kLdsMax; }
+constexpr bool wide_fits(int nt, int ks) { return wide_lds(nt, ks) <= kLdsMax; }
 
 // Column tiles per workgroup for the wide kernel: the widest instantiated divisor
 // of c_out / 16 whose W^T slice fits the LDS; 0 if the wide kernel does not apply.
 int wide_nt(int c_in, int c_out, int elem) {
-  if (elem != 2 || c_in % 8 != 0 || c_out % 16 != 0) return 0;
-  const int ks = wide_ksteps(c_in);
+  if (c_in * elem % 16 != 0 || c_out % 16 != 0) return 0;
+  const int ks = wide_ksteps(c_in, elem);
   if (ks == 0) return 0;
-  const int ldk = 32 * ks + 8;
   const int nt_all = c_out / 16;
-  for (int nt : {16, 12, 8, 6, 4, 3, 2, 1})
-    if (nt_all % nt == 0 && wide_lds(nt, ldk) <= kLdsMax) return nt;
+  for (int nt : {16, 12, 8, 6, 4, 3, 2, 1}) {
+    if (elem == 4 && nt == 16 && ks > 4) continue;  // (float32: the unrolled products spill)
+    if (nt_all % nt == 0 && wide_fits(nt, ks)) return nt;
+  }
   return 0;
 }
 
@@ -923,6 +999,8 @@ const void* wide_kernel(int nt, int ks) {
 }
 
 const void* wide_kernel_for(int dtype, int part_dtype, bool gather, int nt, int ks) {
+  if (dtype == 0 && part_dtype == 0)
+    return gather ? wide_kernel<float, float, true>(nt, ks) : wide_kernel<float, float, false>(nt, ks);
   if (dtype == 1 && part_dtype == 0)
     return gather ? wide_kernel<__half, float, true>(nt, ks) : wide_kernel<__half, float, false>(nt, ks);
   if (dtype == 1 && part_dtype == 1)
@@ -1028,12 +1106,12 @@ hipError_t gemm_t(const GemmLaunchArgs& g, int total_tiles, const void* A, const
 
 }  // namespace
 
-bool gemm_wide_transposed(int c_in, int c_out) { return c_in * c_out >= 128 * 128; }
+bool gemm_wide_transposed(int c_in, int c_out, int dtype) { return dtype != 0 && c_in * c_out >= 128 * 128; }
 
 bool gemm_wide(int c_in, int c_out, int dtype, int part_dtype) {
-  // built for 16-bit operands with partials of the same type or of float32
+  // built for partials of the operands' type or of float32
   const bool pair = part_dtype == dtype || part_dtype == 0;
-  return dtype != 0 && pair && wide_nt(c_in, c_out, 2) > 0;
+  return pair && wide_nt(c_in, c_out, dtype == 0 ? 4 : 2) > 0;
 }
 
 hipError_t launch_transpose_w(const void* w, void* wt, int K3, int c_in, int c_out, hipStream_t s) {
@@ -1094,23 +1172,54 @@ hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const
   int nt = 0, ks = 0, ldk = 0;
   size_t lds = 0;
   if (wide) {
-    // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
-    // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
-    // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
-    nt = wide_nt(c_in, c_out, 2);
-    ks = wide_ksteps(c_in);
-    ldk = 32 * ks + 8;
-    lds = wide_lds(nt, ldk);
-    wfn = wide_kernel_for(dtype, part_dtype, a_rows != nullptr, nt, ks);
-    if (!wfn) return hipErrorInvalidValue;
-    int per_cu = 0, cus = 0;
-    hipError_t e = wide_occupancy(wfn, lds, &per_cu, &cus);
+    const int elem = dtype == 0 ? 4 : 2;
+    nt = wide_nt(c_in, c_out, elem);
+    ks = wide_ksteps(c_in, elem);
+    ldk = (64 * ks + 16) / elem;
+    int64_t slots = 0, cus = 0;
+    auto take = [&](int n) {  // the instance with n column tiles
+      nt = n;
+      lds = wide_lds(nt, ks);
+      wfn = wide_kernel_for(dtype, part_dtype, a_rows != nullptr, nt, ks);
+      if (!wfn) return hipErrorInvalidValue;
+      int per_cu = 0, nc = 0;
+      const hipError_t e = wide_occupancy(wfn, lds, &per_cu, &nc);
+      if (e != hipSuccess) return e;
+      cus = std::max(nc, 1);
+      slots = cus * std::max(per_cu, 1);
+      return hipSuccess;
+    };
+    auto set_rows = [&](int64_t rows, int64_t cap) {
+      const int round = wide_round_rows(nt, ks);
+      rows_per_tile = (int)std::min<int64_t>(std::max<int64_t>((rows + round - 1) / round, 1) * round, cap ? cap : 16 * round);
+    };
+    auto workgroups = [&] {
+      int64_t t = 0;
+      for (int i = 0; i < n_seg; ++i) t += (segs[i].height + rows_per_tile - 1) / rows_per_tile;
+      return t * (c_out / 16 / nt);
+    };
+    hipError_t e = take(nt);
     if (e != hipSuccess) return e;
-    const int64_t slots = (int64_t)std::max(per_cu, 1) * std::max(cus, 1);
-    const int round = wide_round_rows(nt, ks);
-    const int64_t want = tile_rows > 0 ? tile_rows : std::max<int64_t>(512, (rows_all + 2 * slots - 1) / (2 * slots));
-    const int64_t cap = tile_rows > 0 ? (int64_t)1 << 20 : 16 * round;
-    rows_per_tile = (int)std::min<int64_t>(std::max<int64_t>((want + round - 1) / round, 1) * round, cap);
+    if (tile_rows > 0) {
+      set_rows(tile_rows, (int64_t)1 << 20);
+    } else {
+      // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
+      // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
+      // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
+      set_rows(std::max<int64_t>(512, (rows_all + 2 * slots - 1) / (2 * slots)), 0);
+      // Under half the CUs busy: shorter tiles, down to 128 rows, and then narrower
+      // column slices (they read their rows again, from the L2).  Layer times, f16
+      // unless noted: 128 -> 256 stride 2, 113 tiles: 256 rows 30.4 -> 26.1 us; 256 -> 128
+      // transposed, 121 tiles: 29.5 -> 25.0 us; 636 voxels 256 -> 256, 27 tiles: 128 rows
+      // 49.9 -> 37.3, slices of a quarter 33.4 us; 3000 scattered voxels 64 -> 128 float32:
+      // slices of a quarter 18.5 -> 11.6 us.  Above the line both lose: 128 -> 128 with
+      // 240 tiles, 256 rows 34.6 -> 36.4, half slices 38.2 us.
+      for (int rows = 256; rows >= 128 && 2 * workgroups() < cus; rows /= 2) set_rows(rows, 0);
+      while (nt % 2 == 0 && 2 * workgroups() <= cus) {
+        if ((e = take(nt / 2)) != hipSuccess) return e;
+        set_rows(128, 0);
+      }
+    }
   } else if (tile_rows > 0) {
     rows_per_tile = (tile_rows + 15) / 16 * 16;
   } else {
