@@ -379,10 +379,25 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
         for (int i = 0; i < kBatch; ++i) {
           if (i < cnt) {
             const u32x4* wp = sw + (grp * (kOffsetGroup / G) + s[i]) * (KPO * NT * 64) + lane;
+            if constexpr (sizeof(T) == 4) {
+              // a step's sum by itself: one chain over all offsets' channels rounds more.
+              // Error against 64 bits, one chain -> this, and time: 60k LiDAR 32 -> 32 2.4e-7
+              // -> 1.1e-7, 19.1 -> 18.9 us; 16 -> 64 1.7e-7 -> 0.9e-7, 19.5 -> 20.2 us; K = 5
+              // 8 -> 32 2.0e-7 -> 0.9e-7, 30.1 -> 31.0 us (the separate steps: 1.1e-7 and 34.6
+              // us, 0.9e-7 and 36.5 us, 0.9e-7 and 47.2 us).
 #pragma unroll
-            for (int q = 0; q < KPO; ++q)
+              for (int t = 0; t < NT; ++t) {
+                f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-              for (int t = 0; t < NT; ++t) acc[t] = M::mma(wp[(q * NT + t) * 64], a[i][q], acc[t]);
+                for (int q = 0; q < KPO; ++q) part = M::mma(wp[(q * NT + t) * 64], a[i][q], part);
+                acc[t] += part;
+              }
+            } else {
+#pragma unroll
+              for (int q = 0; q < KPO; ++q)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = M::mma(wp[(q * NT + t) * 64], a[i][q], acc[t]);
+            }
           }
         }
       }

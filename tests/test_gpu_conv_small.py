@@ -73,6 +73,11 @@ def test_narrow_layer_matches_oracle(dtype, K, c_in, c_out, mode, n):
     # the separate steps (named by an option) stay within the common tolerance of it
     sep = B.Forward(km, c_in, c_out, B.TORCH_DTYPES[dtype], B.Options.make(gather=B.GATHER_FUSED))(xd, wd)
     assert rel_err(to_f64(sep), to_f64(y)) <= TOL[dtype]
+    if dtype == "f32" and n >= 2000:
+        # both sum an offset's channels first and then the offsets, so their errors differ
+        # by chance only, over 32,000 outputs or more; one chain over both is 1.5 to 2 times
+        # as far off
+        assert np.linalg.norm(to_f64(y) - ref) <= 1.25 * np.linalg.norm(to_f64(sep) - ref)
     res = scenes.features(km.n_out, c_out, dtype, 7)
     ye = f(xd, wd, residual=to_dev(res, dtype), relu=True)
     assert rel_err(to_f64(ye), np.maximum(ref + scenes.to_f64(res, dtype), 0.0)) <= 2 * ROUNDING[dtype]
