@@ -132,6 +132,10 @@ def kernel_models(n, n_out, pairs, L, k3, passes, fused=True, pelem=None, centre
         "k_gemm_bytes": ("hbm", (pg * L.c_in * e if not fused else n * L.c_in * e + 4 * pg)
                          + pg * L.c_out * ep + (k3 - (1 if centre else 0)) * L.c_in * L.c_out * e),
         "k_gemm_flops": ("mfma", 2.0 * pg * L.c_in * L.c_out),
+        # narrow layers in one kernel: input rows and weights once, one table entry per
+        # (offset, output), one row index per pair, the row map, the output
+        "k_conv_small": ("hbm", n * L.c_in * e + k3 * L.c_in * L.c_out * e + 4 * n_out * (k3 + 1) + 4 * pairs
+                         + n_out * L.c_out * e),
         # scatter with the centre offset: each output's own input row, the other offsets'
         # partial rows, one table entry per (offset, output), the row map, W_c, the output
         "k_scatter_centre": ("hbm", n_out * L.c_in * e + pg * L.c_out * ep + n_out * L.c_out * e
@@ -407,8 +411,8 @@ def main():
     gmas_ms = sum(ph_ms.get(p, 0.0) for p in GMAS_PHASES)
     n, n_out, pairs = lb.n, lb.n_out, lb.pairs
     map_bytes = 28 * n + 8 * n_out + 12 * n + 8 * pairs + 4 * (k3 + 1)
-    gemm_ms = kern.get("k_gemm", (float("nan"), 1))[0]
-    gemm_tflops = models["k_gemm_flops"][1] / (gemm_ms * 1e-3) / 1e12
+    # narrow layers run as one kernel and have no GEMM launch
+    gemm_tflops = models["k_gemm_flops"][1] / (kern["k_gemm"][0] * 1e-3) / 1e12 if "k_gemm" in kern else None
     pname = "f32" if lb.pelem == 4 else L.dtype
 
     out = {
@@ -432,8 +436,8 @@ def main():
         "phases_ms": {k: round(v, 5) for k, v in ph_ms.items()},
         "kernels_ms_per_step": {k: round(v[0], 5) for k, v in sorted(kern.items(), key=lambda t: -t[1][0])},
         "map_gbps_compulsory": round(map_bytes / (map_ms * 1e-3) / 1e9, 2),
-        "gemm_tflops": round(gemm_tflops, 3),
-        "gemm_frac_mfma": round(gemm_tflops / MFMA_PEAK_TFLOPS[L.dtype], 5),
+        "gemm_tflops": None if gemm_tflops is None else round(gemm_tflops, 3),
+        "gemm_frac_mfma": None if gemm_tflops is None else round(gemm_tflops / MFMA_PEAK_TFLOPS[L.dtype], 5),
         "padding_overhead": (lb.plan.rows_padded - lb.plan.rows_real) / max(lb.plan.rows_real, 1),
         "gemm_launches": lb.plan.n_gemm_launches,
         "gather": args.gather,
