@@ -266,6 +266,8 @@ struct GemmSeg {
 // transposed beforehand (large W_k; small ones are transposed while staging).
 bool gemm_wide(int c_in, int c_out, int dtype, int part_dtype);
 bool gemm_wide_transposed(int c_in, int c_out, int dtype);
+void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, int64_t cus, int64_t per_cu, int* nt,
+                int* rows);
 // wt[k][n][c] = w[k][c][n] for 16-bit weights.
 hipError_t launch_transpose_w(const void* w, void* wt, int K3, int c_in, int c_out, hipStream_t s);
 // Launches the segments (any number; split into launches of at most 64 segments).

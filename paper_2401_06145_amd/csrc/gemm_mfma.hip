@@ -206,7 +206,7 @@ constexpr size_t wide_lds(int nt, int ks) { return (size_t)16 * nt * (64 * ks + 
 // CG * NTW column tiles, the others take further rows.  Two row blocks per wave
 // while their operands (and the next blocks' in flight) take at most 128
 // registers and the layer is wide enough for the LDS reads to matter: 65 to 128
-// input channels (from 160 channels the two blocks and their successors in
+// input channels of 16 bits (from 160 channels the two blocks and their successors in
 // flight need 160 registers and the kernel spills).  The columns of a two-block
 // wave are produced in NCH chunks of at most 8 tiles, so that operands,
 // accumulators and fragments stay within the 256 registers a wave has at two
@@ -223,8 +223,8 @@ constexpr int wide_nch(int ntw, int mb, int ksteps) {
   return nch;
 }
 
-// NT = 16-column tiles per workgroup; KSTEPS >= c_in / 32 k-steps of 32 (k past
-// c_in is zero).  w is W, [K^3][c_in][c_out]; wt is NULL or W^T, [K^3][c_out][c_in]
+// NT = 16-column tiles per workgroup; KSTEPS k-steps of 64 bytes, 32 16-bit or 16 float32
+// channels (k past c_in is zero).  w is W, [K^3][c_in][c_out]; wt is NULL or W^T, [K^3][c_out][c_in]
 // (then W_k^T is staged from it with 16-byte copies); dump is one spare
 // row of c_out partials that absorbs the stores of rows without data.  Loads
 // never branch: lanes without data (rows past the segment, k past c_in) read a
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   static_assert(E * sizeof(T) == 16 && KS == 4 * E, "16-byte fragments");
   constexpr int CG = wide_cg(NT);
   constexpr int NTW = NT / CG;
-  constexpr int MB = wide_mb(NTW, KSTEPS);
+  constexpr int MB = wide_mb((int)sizeof(T), KSTEPS);
   constexpr int NCH = wide_nch(NTW, MB, KSTEPS);
   constexpr int NTC = NTW / NCH;  // column tiles per chunk
   static_assert(NTW % NCH == 0, "chunks must split the tiles");
@@ -979,10 +979,7 @@ int wide_nt(int c_in, int c_out, int elem) {
 }
 
 // Rows of one round of the workgroup (tiles are whole rounds).
-int wide_round_rows(int nt, int ks) {
-  const int cg = wide_cg(nt);
-  return kWideWaves / cg * wide_mb(nt / cg, ks) * 16;
-}
+int wide_round_rows(int nt, int ks, int elem) { return kWideWaves / wide_cg(nt) * wide_mb(elem, ks) * 16; }
 
 template <typename T, typename TO, bool GATHER>
 const void* wide_kernel(int nt, int ks) {
@@ -1160,13 +1157,47 @@ hipError_t wide_occupancy(const void* fn, size_t lds, int* per_cu, int* cus, int
   return hipSuccess;
 }
 
+// Shape of a launch's tiles: column tiles per workgroup (nt) and rows per tile.  cus and
+// per_cu: the card's CUs, and workgroups of the widest instance that one holds.
+void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, int64_t cus, int64_t per_cu, int* nt,
+                int* rows) {
+  *nt = wide_nt(c_in, c_out, elem);
+  const int round = wide_round_rows(*nt, wide_ksteps(c_in, elem), elem);
+  int64_t all = 0;
+  for (int i = 0; i < n_seg; ++i) all += segs[i].height;
+  auto set_rows = [&](int64_t r) {
+    *rows = (int)(std::min<int64_t>(std::max<int64_t>((r + round - 1) / round, 1), 16) * round);
+  };
+  auto workgroups = [&] {
+    int64_t t = 0;
+    for (int i = 0; i < n_seg; ++i) t += (segs[i].height + *rows - 1) / *rows;
+    return t * (c_out / 16 / *nt);
+  };
+  // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
+  // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
+  // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
+  set_rows(std::max<int64_t>(512, (all + 2 * cus * per_cu - 1) / (2 * cus * per_cu)));
+  // Under half the CUs busy: shorter tiles, down to 128 rows, and then narrower
+  // column slices (they read their rows again, from the L2).  Layer times, f16
+  // unless noted: 128 -> 256 stride 2, 113 tiles: 256 rows 30.4 -> 26.1 us; 256 -> 128
+  // transposed, 121 tiles: 29.5 -> 25.0 us; 636 voxels 256 -> 256, 27 tiles: 128 rows
+  // 49.9 -> 37.3, slices of a quarter 33.4 us; 3000 scattered voxels 64 -> 128 float32:
+  // slices of a quarter 18.5 -> 11.6 us.  From the line up both lose: 128 -> 128 with
+  // 240 tiles, 256 rows 34.6 -> 36.4, half slices 38.2 us; at exactly half, half slices of
+  // 128 rows: 384 -> 256 stride 2 34.2 -> 39.8 us, 512 -> 192, K = 1, 39.2 -> 44.9 us.
+  for (int r = 256; r >= 128 && 2 * workgroups() < cus; r /= 2)
+    if (r < *rows) set_rows(r);
+  while (*nt % 2 == 0 && 2 * workgroups() < cus) {
+    *nt /= 2;
+    set_rows(128);
+  }
+}
+
 hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const int32_t* a_rows, const void* w,
                        const void* wt, void* buf_out, void* dump_row, int c_in, int c_out, int dtype, int part_dtype,
                        int tile_rows, bool stream, hipStream_t s) {
   if (c_out % 16 != 0) return hipErrorInvalidValue;
   const bool wide = dump_row && gemm_wide(c_in, c_out, dtype, part_dtype);
-  int64_t rows_all = 0;
-  for (int i = 0; i < n_seg; ++i) rows_all += segs[i].height;
   int rows_per_tile = 64;
   const void* wfn = nullptr;
   int nt = 0, ks = 0, ldk = 0;
@@ -1176,54 +1207,28 @@ hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const
     nt = wide_nt(c_in, c_out, elem);
     ks = wide_ksteps(c_in, elem);
     ldk = (64 * ks + 16) / elem;
-    int64_t slots = 0, cus = 0;
-    auto take = [&](int n) {  // the instance with n column tiles
-      nt = n;
+    auto instance = [&] {
       lds = wide_lds(nt, ks);
       wfn = wide_kernel_for(dtype, part_dtype, a_rows != nullptr, nt, ks);
-      if (!wfn) return hipErrorInvalidValue;
-      int per_cu = 0, nc = 0;
-      const hipError_t e = wide_occupancy(wfn, lds, &per_cu, &nc);
-      if (e != hipSuccess) return e;
-      cus = std::max(nc, 1);
-      slots = cus * std::max(per_cu, 1);
-      return hipSuccess;
+      return wfn ? hipSuccess : hipErrorInvalidValue;
     };
-    auto set_rows = [&](int64_t rows, int64_t cap) {
-      const int round = wide_round_rows(nt, ks);
-      rows_per_tile = (int)std::min<int64_t>(std::max<int64_t>((rows + round - 1) / round, 1) * round, cap ? cap : 16 * round);
-    };
-    auto workgroups = [&] {
-      int64_t t = 0;
-      for (int i = 0; i < n_seg; ++i) t += (segs[i].height + rows_per_tile - 1) / rows_per_tile;
-      return t * (c_out / 16 / nt);
-    };
-    hipError_t e = take(nt);
+    hipError_t e = instance();
     if (e != hipSuccess) return e;
     if (tile_rows > 0) {
-      set_rows(tile_rows, (int64_t)1 << 20);
+      const int round = wide_round_rows(nt, ks, elem);
+      rows_per_tile = (tile_rows + round - 1) / round * round;
     } else {
-      // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
-      // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
-      // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
-      set_rows(std::max<int64_t>(512, (rows_all + 2 * slots - 1) / (2 * slots)), 0);
-      // Under half the CUs busy: shorter tiles, down to 128 rows, and then narrower
-      // column slices (they read their rows again, from the L2).  Layer times, f16
-      // unless noted: 128 -> 256 stride 2, 113 tiles: 256 rows 30.4 -> 26.1 us; 256 -> 128
-      // transposed, 121 tiles: 29.5 -> 25.0 us; 636 voxels 256 -> 256, 27 tiles: 128 rows
-      // 49.9 -> 37.3, slices of a quarter 33.4 us; 3000 scattered voxels 64 -> 128 float32:
-      // slices of a quarter 18.5 -> 11.6 us.  Above the line both lose: 128 -> 128 with
-      // 240 tiles, 256 rows 34.6 -> 36.4, half slices 38.2 us.
-      for (int rows = 256; rows >= 128 && 2 * workgroups() < cus; rows /= 2) set_rows(rows, 0);
-      while (nt % 2 == 0 && 2 * workgroups() <= cus) {
-        if ((e = take(nt / 2)) != hipSuccess) return e;
-        set_rows(128, 0);
-      }
+      int per_cu = 0, cus = 0;
+      if ((e = wide_occupancy(wfn, lds, &per_cu, &cus)) != hipSuccess) return e;
+      wide_tiles(segs, n_seg, c_in, c_out, elem, std::max(cus, 1), std::max(per_cu, 1), &nt, &rows_per_tile);
+      if ((e = instance()) != hipSuccess) return e;
     }
   } else if (tile_rows > 0) {
     rows_per_tile = (tile_rows + 15) / 16 * 16;
   } else {
     // enough workgroups to fill 256 CUs several times, at most 1024 rows each
+    int64_t rows_all = 0;
+    for (int i = 0; i < n_seg; ++i) rows_all += segs[i].height;
     while (rows_per_tile < 1024 && rows_all / (rows_per_tile * 2) >= 2048) rows_per_tile *= 2;
   }
   for (int base = 0; base < n_seg; base += kMaxSegPerLaunch) {

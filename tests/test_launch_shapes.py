@@ -1,0 +1,44 @@
+"""Host-side rules that shape launches: column tiles and rows per tile of the full-width
+matrix product.  No GPU: the rules take the card's sizes as arguments."""
+import ctypes
+
+import pytest
+
+from paper_2401_06145_amd import binding as B
+
+CUS = 256
+
+
+class _Seg(ctypes.Structure):
+    _fields_ = [("k", ctypes.c_int), ("row0", ctypes.c_int64), ("rows", ctypes.c_int64), ("height", ctypes.c_int64)]
+
+
+def _wide_tiles(heights, c_in, c_out, elem, per_cu=1):
+    segs, at = (_Seg * len(heights))(), 0
+    for i, h in enumerate(heights):
+        segs[i] = _Seg(i, at, h, h)
+        at += h
+    nt, rows = ctypes.c_int(), ctypes.c_int()
+    i64, c_int = ctypes.c_int64, ctypes.c_int
+    # void spc::wide_tiles(const GemmSeg*, int, int, int, int, int64_t, int64_t, int*, int*)
+    B.lib()._ZN3spc10wide_tilesEPKNS_7GemmSegEiiiillPiS3_(
+        segs, c_int(len(heights)), c_int(c_in), c_int(c_out), c_int(elem), i64(CUS), i64(per_cu), ctypes.byref(nt),
+        ctypes.byref(rows))
+    return nt.value, rows.value, sum(-(-h // rows.value) for h in heights) * (c_out // 16 // nt.value)
+
+
+@pytest.mark.parametrize("heights,c_in,c_out,nt,rows", [
+    ([4096] * 8, 384, 256, 8, 512),     # K = 2 stride 2, two slices: 128 workgroups
+    ([32768], 512, 192, 6, 512),        # K = 1, two slices: 128 workgroups
+    ([512] * 128, 32, 64, 4, 512),      # one slice
+])
+def test_half_the_card_keeps_its_tiles(heights, c_in, c_out, nt, rows):
+    """Exactly half the CUs with a workgroup: tiles stay at 512 rows and the full slice."""
+    assert _wide_tiles(heights, c_in, c_out, 2) == (nt, rows, CUS // 2)
+
+
+def test_fewer_workgroups_shrink_tiles_then_slices():
+    nt, rows, wg = _wide_tiles([500] * 127, 64, 128, 2)     # one short of half
+    assert (nt, rows) == (8, 256) and wg >= CUS // 2
+    nt, rows, wg = _wide_tiles([600], 256, 256, 2)
+    assert (nt, rows) == (1, 128) and wg == 5 * 16
