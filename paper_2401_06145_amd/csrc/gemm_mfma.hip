@@ -214,9 +214,10 @@ constexpr size_t wide_lds(int nt, int ks) { return (size_t)16 * nt * (64 * ks + 
 // operands alone take 128 registers there).  Measured on gfx950: C = 128 GEMM 0.142 -> 0.132 ms; at C = 64
 // one block per wave is faster (26.5 vs 28.5 us on the 120k LiDAR layer), at
 // C = 32 the two are equal; one block per wave stays faster in one chunk; CG > 1
-// cost more occupancy than it saved.
+// cost more occupancy than it saved.  float32 stays at one block: its products take four
+// times as long per fragment read, and with two a tile has 256 rows at the least.
 constexpr int wide_cg(int) { return 1; }
-constexpr int wide_mb(int, int ksteps) { return (ksteps == 3 || ksteps == 4) ? 2 : 1; }
+constexpr int wide_mb(int elem, int ksteps) { return (elem == 2 && (ksteps == 3 || ksteps == 4)) ? 2 : 1; }
 constexpr int wide_nch(int ntw, int mb, int ksteps) {
   int nch = 1;
   while ((mb > 1 || ksteps >= 16) && ntw / nch > (mb > 1 ? 8 : 2) && ntw % (2 * nch) == 0) nch *= 2;
@@ -1176,7 +1177,15 @@ void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, i
   // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
   // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
   // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
-  set_rows(std::max<int64_t>(512, (all + 2 * cus * per_cu - 1) / (2 * cus * per_cu)));
+  int64_t least = 512;
+  // float32: its products take 16 times the time of 16-bit ones, so that the longest
+  // tile sets the time of small launches, and of those with one long segment among short
+  // ones (the centre offset of scattered voxels).  One slice of a tile per CU, from 128
+  // rows up to the 512.  8001 scattered voxels, K = 5, 256 -> 128: 512 rows 114.9, 128 rows
+  // 63.7 us; 2000, K = 3, 128 -> 512: 47.9 and 21.3.  Over 180 layers of 65k to 131k pairs
+  // 512 rows took 0.89 times the time of 128, over 140 of 16k to 33k 1.43 times.
+  if (elem == 4) least = std::min<int64_t>(512, std::max<int64_t>(128, all * (c_out / 16 / *nt) / cus));
+  set_rows(std::max<int64_t>(least, (all + 2 * cus * per_cu - 1) / (2 * cus * per_cu)));
   // Under half the CUs busy: shorter tiles, down to 128 rows, and then narrower
   // column slices (they read their rows again, from the L2).  Layer times, f16
   // unless noted: 128 -> 256 stride 2, 113 tiles: 256 rows 30.4 -> 26.1 us; 256 -> 128

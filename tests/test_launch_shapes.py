@@ -42,3 +42,17 @@ def test_fewer_workgroups_shrink_tiles_then_slices():
     assert (nt, rows) == (8, 256) and wg >= CUS // 2
     nt, rows, wg = _wide_tiles([600], 256, 256, 2)
     assert (nt, rows) == (1, 128) and wg == 5 * 16
+
+
+@pytest.mark.parametrize("heights,c_in,c_out,rows", [
+    ([2000] + [15] * 26, 128, 512, 128),      # scattered voxels: one long segment
+    ([8001] + [60] * 63, 256, 128, 128),
+    ([3000] * 8, 64, 64, 128),                # 94 rows for each CU
+    ([20000] * 4, 64, 64, 384),               # 312 rows for each CU
+    ([20000] * 4, 64, 512, 512),
+    ([120000] + [8000] * 26, 64, 64, 768),    # 641 rows for each of two rounds of tiles
+])
+def test_float32_tiles_follow_the_work(heights, c_in, c_out, rows):
+    """float32 tiles hold one CU's share of the rows times column slices, 128 to 512 rows
+    (whole rounds of 128), before the rule for large launches."""
+    assert _wide_tiles(heights, c_in, c_out, 4)[1] == rows
