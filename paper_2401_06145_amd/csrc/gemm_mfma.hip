@@ -971,6 +971,12 @@ int wide_nt(int c_in, int c_out, int elem) {
   if (c_in * elem % 16 != 0 || c_out % 16 != 0) return 0;
   const int ks = wide_ksteps(c_in, elem);
   if (ks == 0) return 0;
+  // float32 is bound by its products: the k-steps may hold at most a third more channels
+  // than the layer has, and no layer is narrower than one (k_gemm has steps of 4
+  // channels).  Times of k_gemm's, over 120 layers each: 4 channels 1.01 (2000 scattered
+  // voxels, K = 4, 4 -> 512: 23.9 against 12.8 us), 8 channels 0.99 with a fifth of them
+  // over 1.05; 12 and 20 channels 0.93 and 0.92, up to 1.19; 16 and 36 0.91 and 0.86.
+  if (elem == 4 && (c_in < 16 || 16 * ks * 3 > 4 * c_in)) return 0;
   const int nt_all = c_out / 16;
   for (int nt : {16, 12, 8, 6, 4, 3, 2, 1}) {
     if (elem == 4 && nt == 16 && ks > 4) continue;  // (float32: the unrolled products spill)

@@ -56,3 +56,14 @@ def test_float32_tiles_follow_the_work(heights, c_in, c_out, rows):
     """float32 tiles hold one CU's share of the rows times column slices, 128 to 512 rows
     (whole rounds of 128), before the rule for large launches."""
     assert _wide_tiles(heights, c_in, c_out, 4)[1] == rows
+
+
+@pytest.mark.parametrize("c_in,wide", [(4, False), (8, False), (12, False), (16, True), (20, False), (24, True),
+                                       (36, True), (64, True), (68, False), (72, True), (132, False), (144, True),
+                                       (256, True), (260, False)])
+def test_float32_full_width_pads_a_third_at_most(c_in, wide):
+    """k-steps of 16 channels (1, 2, 3, 4, 6, 8, 12 or 16 of them): layers that would pad more
+    than a third, or fill less than one step, keep the general product."""
+    gemm_wide = B.lib()._ZN3spc9gemm_wideEiiii
+    gemm_wide.restype = ctypes.c_bool
+    assert gemm_wide(c_in, 64, B.SPCONV_F32, B.SPCONV_F32) == wide
