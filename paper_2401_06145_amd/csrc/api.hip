@@ -975,9 +975,8 @@ int forward_impl(const spconv_map* m, const void* d_x, const void* d_w, void* d_
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (one_kernel(m, d_x, d_w, d_y, c_in, c_out, p, opt)) {
     PhaseScope ph(PH_GEMM, s);
-    const bool stream = m->n_out * c_out * p.elem >= kStreamOutputBytes;
     SPC_TRY(launch_conv_small(d_x, m->n_in, d_w, m->pin, m->omt, m->omt_stride, m->out_perm, m->K3, d_y, d_residual,
-                              relu, m->n_out, c_in, c_out, dtype, stream, s),
+                              relu, m->n_out, c_in, c_out, dtype, s),
             "one-kernel convolution");
     return SPCONV_OK;
   }

@@ -148,7 +148,7 @@ struct ConvArgs {
   const uint32_t* perm;   // caller row of each sorted output (NULL: identity)
   void* y;
   const void* residual;
-  int K3, n_out, c_in, c_out, relu, stream;
+  int K3, n_out, c_in, c_out, relu;
   uint32_t row_bytes, x_bytes;
 };
 
@@ -402,7 +402,10 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
         }
       }
     }
-    // each lane holds, for its row, columns 4 sub .. + 3 of every tile
+    // each lane holds, for its row, columns 4 sub .. + 3 of every tile.  Plain stores: a
+    // store writes 64 bytes of each of 16 rows, parts of lines that the caches
+    // gather; non-temporal ones took 300k rows, K = 1, 48 -> 128 from 26.7 to 31.4 us, over 148
+    // layers with outputs of 64 MiB and more 1.11 times as long.
     if (p < g.n_out) {
       constexpr int W = Out<T>::N;  // channels per 16-byte vector
       constexpr int TV = W / 4;     // tiles per vector
@@ -420,11 +423,7 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
 #pragma unroll
           for (int i = 0; i < W; ++i) s[i] = fmaxf(s[i], 0.f);
         }
-        const uint4 out = Out<T>::pack(s);
-        if (g.stream)
-          store_stream(y + o, out);
-        else
-          *reinterpret_cast<uint4*>(y + o) = out;
+        *reinterpret_cast<uint4*>(y + o) = Out<T>::pack(s);
       }
       if constexpr (NT % TV != 0) {  // the last tile of an odd count: 4 channels, 8 bytes
         const int64_t o = at + 16 * (NT - 1) + 4 * sub;
@@ -440,10 +439,7 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
           for (int i = 0; i < 4; ++i) s[i] = fmaxf(s[i], 0.f);
         }
         const uint4 out = Out<T>::pack(s);
-        if (g.stream)
-          store_stream(y + o, make_uint2(out.x, out.y));
-        else
-          *reinterpret_cast<uint2*>(y + o) = make_uint2(out.x, out.y);
+        *reinterpret_cast<uint2*>(y + o) = make_uint2(out.x, out.y);
       }
     }
   }
@@ -505,7 +501,7 @@ bool conv_small_applies(int64_t n_in, int64_t n_out, int K3, int c_in, int c_out
 
 hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
                              int64_t mt_stride, const uint32_t* perm, int K3, void* y, const void* residual, int relu,
-                             int64_t n_out, int c_in, int c_out, int dtype, bool stream, hipStream_t s) {
+                             int64_t n_out, int c_in, int c_out, int dtype, hipStream_t s) {
   if (n_out <= 0) return hipSuccess;
   const ConvShape sh = conv_shape(n_out, K3, c_in, c_out, dtype);
   if (!sh.fn || n_out >= ((int64_t)1 << 31) - 1024) return hipErrorInvalidValue;
@@ -524,7 +520,6 @@ hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const i
   g.c_in = c_in;
   g.c_out = c_out;
   g.relu = relu;
-  g.stream = stream ? 1 : 0;
   g.row_bytes = (uint32_t)(c_in * (dtype == 0 ? 4 : 2));
   g.x_bytes = (uint32_t)n_in * g.row_bytes;
   // one workgroup per CU, about four blocks per workgroup on small clouds; a multiple of

@@ -116,3 +116,18 @@ def test_output_over_the_input():
     f = B.Forward(km, 16, 16, torch.float32)
     assert f(xd, wd, y=xd) is xd
     assert rel_err(to_f64(xd), ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 16, 128), ("f32", 16, 64)])
+def test_output_of_64_mib(dtype, c_in, c_out):
+    """Outputs past the size from which the scatter streams its rows.  One offset, so that
+    every output is one product: 2^-11 or float32 rounding of 16 terms."""
+    say(f"output of 64 MiB {dtype}")
+    coords = _cloud(79, 300_001, 70)
+    km = B.KernelMap.build(to_dev(coords), 1)
+    x = to_dev(scenes.features(km.n_in, c_in, dtype, 3), dtype)
+    w = to_dev(scenes.weights(1, c_in, c_out, dtype, 4), dtype)
+    y = B.Forward(km, c_in, c_out, B.TORCH_DTYPES[dtype])(x, w)
+    assert y.numel() * y.element_size() >= 1 << 26
+    ref = x.double() @ w[0].double()
+    assert float((y.double() - ref).abs().max() / ref.abs().max()) <= ROUNDING[dtype]
