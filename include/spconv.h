@@ -213,11 +213,16 @@ size_t spconv_forward_workspace_bytes(const spconv_map* m, int c_in, int c_out, 
  * Requirements: c_in, c_out in [1, 1024]; 16-byte rows (c * element size % 16 == 0)
  * and c_out % 16 == 0; d_x, d_w, d_y (and d_residual) 16-byte aligned, else
  * SPCONV_EINVAL.  Asynchronous on `stream`; no host synchronisation.
- * Narrow layers, whose K^3 weight matrices fit the LDS of a CU, run as one kernel that
- * sums every offset's products in float32 and never forms GEMM partials, unless an option
- * names a form of the separate steps (gather, centre, partial_dtype, t_gather or
- * t_scatter given) or d_y overlaps d_x or d_w; grouping and gemm_tile_rows have nothing
- * to shape there.
+ * Narrow layers run as one kernel that sums every offset's products in float32 and never
+ * forms GEMM partials: c_out 16, 32, 48, 64, 96 or 128, c_in up to 128 (float32 64), all
+ * K^3 weight matrices in the LDS of a CU, inputs of at most 3.5 GiB, and of those the
+ * layers that take less time that way, by their widths, outputs and pairs.  (K = 3, 16
+ * bits: up to 32 -> 64, 64 -> 32 or 16 -> 128; float32 up to 16 -> 64, or 32 -> 32 from 4
+ * pairs per output.)  Results differ from the separate steps' by the rounding of partials.
+ * An option that names a form of the separate steps (gather, centre, partial_dtype,
+ * t_gather or t_scatter given) keeps them, and so does a d_y that overlaps d_x or d_w;
+ * grouping and gemm_tile_rows have nothing to shape in one kernel.  The workspace is
+ * sized for the separate steps in every case.
  * A SPCONV_SUBM map with odd K builds the input-side metadata table of Algorithm
  * 1's gather lazily: the first call that gathers through the table (gather =
  * SPCONV_GATHER_BUFFER) fills it from the pair lists on its `stream`, so calls on

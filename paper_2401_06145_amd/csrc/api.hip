@@ -519,7 +519,8 @@ bool one_kernel(const spconv_map* m, const void* x, const void* w, const void* y
                 const GmasPlan& p, const spconv_options* opt) {
   // options that name a form of the separate steps keep them
   if (opt && (opt->centre || opt->gather || opt->partial_dtype || opt->t_gather || opt->t_scatter)) return false;
-  if (p.rows_pairs == 0 || !m->omt || !conv_small_applies(m->n_in, m->n_out, m->K3, c_in, c_out, p.dtype)) return false;
+  if (p.rows_pairs == 0 || !m->omt || !conv_small_applies(m->n_in, m->n_out, p.rows_pairs, m->K3, c_in, c_out, p.dtype))
+    return false;
   // outputs are written while other workgroups still read inputs and weights
   auto apart = [](const void* a, int64_t na, const void* b, int64_t nb) {
     const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
@@ -975,8 +976,8 @@ int forward_impl(const spconv_map* m, const void* d_x, const void* d_w, void* d_
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (one_kernel(m, d_x, d_w, d_y, c_in, c_out, p, opt)) {
     PhaseScope ph(PH_GEMM, s);
-    SPC_TRY(launch_conv_small(d_x, m->n_in, d_w, m->pin, m->omt, m->omt_stride, m->out_perm, m->K3, d_y, d_residual,
-                              relu, m->n_out, c_in, c_out, dtype, s),
+    SPC_TRY(launch_conv_small(d_x, m->n_in, d_w, m->pin, m->omt, m->omt_stride, m->out_perm, p.rows_pairs, m->K3,
+                              d_y, d_residual, relu, m->n_out, c_in, c_out, dtype, s),
             "one-kernel convolution");
     return SPCONV_OK;
   }

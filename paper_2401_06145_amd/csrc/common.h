@@ -293,10 +293,12 @@ hipError_t launch_scatter_centre(const void* x, const uint32_t* perm, const void
                                  int part_dtype, bool stream, hipStream_t s);
 
 // conv_small.hip: the whole GMaS step of a narrow layer in one kernel, without partial
-// rows.  Whether an instance serves the layer, and the launcher.
-bool conv_small_applies(int64_t n_in, int64_t n_out, int K3, int c_in, int c_out, int dtype);
+// rows.  Whether an instance serves the layer and takes less time than the separate
+// steps, and the launcher.  pairs: all pairs of the map.
+bool conv_small_applies(int64_t n_in, int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype);
 hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
-                             int64_t mt_stride, const uint32_t* perm, int K3, void* y, const void* residual, int relu,
-                             int64_t n_out, int c_in, int c_out, int dtype, hipStream_t s);
+                             int64_t mt_stride, const uint32_t* perm, int64_t pairs, int K3, void* y,
+                             const void* residual, int relu, int64_t n_out, int c_in, int c_out, int dtype,
+                             hipStream_t s);
 
 }  // namespace spc

@@ -470,40 +470,64 @@ ConvShape conv_shape_k(int K3, int nt, int kpo, int gr) {
   return K3 <= 8 ? conv_shape_t<T, 2>(K3, nt, kpo, gr) : conv_shape_t<T, 7>(K3, nt, kpo, gr);
 }
 
-// Which layers: the K^3 weight matrices fit the LDS beside the row lists (16-bit K = 3:
-// up to 32 -> 64 or 48 x 48 channels; K = 2: 96 -> 96 or 64 -> 128), and
-//  * the row is at least half as wide as the input (each block's input rows are
-//    requested once per offset whatever the width: 128 -> 16, K = 3, 183k voxels took
-//    48.4 us against the separate steps' 43.2);
-//  * float32 (K > 1): at most 4 k-steps x tiles per offset, 2 on clouds of under 512
-//    blocks.  A block's products run in one wave, at every offset that any of its rows
-//    lists (all eight for transposed K = 2 maps), and float32 MFMAs take twice the
-//    cycles for an eighth of the work: 64 -> 64, K = 2, 86k voxels 37.5 against 34.6 us;
-//    32 -> 32, K = 3, 1.7k voxels 13.6 against 11.5, 60k voxels 18.5 against 34.7.
-ConvShape conv_shape(int64_t n_out, int K3, int c_in, int c_out, int dtype) {
+// Which layers.  kpo k-steps of 64 bytes of input channels per offset (narrower inputs put
+// two or four offsets into one), nt tiles of 16 output channels:
+//  * the K^3 weight matrices, c_in padded to whole k-steps, fit the LDS beside the row lists:
+//    16-bit K = 3: kpo * nt <= 4 (32 -> 64, 64 -> 32); 16 -> 128; K = 2: 96 -> 96, 64 -> 128;
+//    K = 5: 32 -> 16, 16 -> 32, 8 -> 64;
+//  * kpo <= 2 nt (each block's input rows are requested once per offset whatever the
+//    width: 128 -> 16, K = 3, 183k voxels took 48.4 us against the separate steps' 43.2;
+//    48 and 64 -> 16, K = 3: 0.77 times their time over 60 layers).  K = 1 in 16 bits and widths
+//    that the centre scatter takes, one launch as well: kpo < 2 nt (128 -> 32, 179k voxels
+//    15.2 against 14.3 us);
+//  * 16 bits, under 512 blocks and 4 pairs per output: at most 64 KiB of weights, which
+//    every workgroup stages (500 voxels, K = 3, 32 -> 64 9.4 against 7.9 us, K = 2, 64 -> 128
+//    8.9 against 6.5; 54 KiB, K = 3, 32 -> 32, never over 1.02; with 7.4 pairs per output
+//    32 -> 64 never);
+//  * float32 (K > 1): kpo * nt <= 4, 2 under 512 blocks.  A block's products run in one
+//    wave, at every offset that any of its rows lists, and float32 MFMAs take twice the
+//    cycles for an eighth of the work: 64 -> 64, K = 2, 86k voxels 37.5 against 34.6 us.
+//    From K = 3 the separate steps, which multiply listed pairs only, win where few of a
+//    block's rows share an offset.  Under 4 pairs per output: kpo = 1 (32 -> 32, 120k LiDAR
+//    voxels 38.2 against 32.7 us, room down 70.9 against 51.7; at 5.6 pairs, 30k LiDAR 13.5
+//    against 22.9); under 512 blocks nt = 1 (16 -> 32, 2k voxels 9.1 against 8.3 us), or 2
+//    with four offsets per step; and under 1.2 pairs kpo * nt <= 3 (scattered voxels, stride
+//    2, 16 -> 64 35.4 against 30.8 us).
+ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
   if (c_out % 16 != 0) return ConvShape{};
   const int ks = dtype == 0 ? 16 : 32;  // channels per k-step
   const int gr = c_in * 4 <= ks ? 4 : (c_in * 2 <= ks ? 2 : 1);
   const int kpo = gr > 1 ? 1 : (c_in + ks - 1) / ks;
   if (gr > 1 && c_in * gr != ks) return ConvShape{};
   const int nt = c_out / 16;
-  if (kpo > 2 * nt || (dtype == 0 && K3 > 1 && kpo * nt > (n_out < 512 * 16 ? 2 : 4))) return ConvShape{};
-  if (dtype == 0) return conv_shape_k<float>(K3, c_out / 16, kpo, gr);
-  if (dtype == 1) return conv_shape_k<__half>(K3, c_out / 16, kpo, gr);
-  return conv_shape_k<__hip_bfloat16>(K3, c_out / 16, kpo, gr);
+  if (kpo > 2 * nt) return ConvShape{};
+  const bool few = n_out < 512 * 16, sparse = pairs < 4 * n_out;
+  if (dtype != 0) {
+    if (K3 == 1 && c_out % 32 == 0 && kpo >= 2 * nt) return ConvShape{};
+    if (K3 > 1 && few && sparse && (K3 + gr - 1) / gr * kpo * nt > 64) return ConvShape{};
+  } else if (K3 > 1) {
+    if (kpo * nt > (few ? 2 : 4)) return ConvShape{};
+    if (K3 >= 27 && sparse &&
+        (kpo > 1 || (few && nt > 1 && gr < 4) || (kpo * nt == 4 && gr == 1 && 5 * pairs < 6 * n_out)))
+      return ConvShape{};
+  }
+  if (dtype == 0) return conv_shape_k<float>(K3, nt, kpo, gr);
+  if (dtype == 1) return conv_shape_k<__half>(K3, nt, kpo, gr);
+  return conv_shape_k<__hip_bfloat16>(K3, nt, kpo, gr);
 }
 
 }  // namespace
 
-bool conv_small_applies(int64_t n_in, int64_t n_out, int K3, int c_in, int c_out, int dtype) {
-  return conv_shape(n_out, K3, c_in, c_out, dtype).fn && n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes;
+bool conv_small_applies(int64_t n_in, int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
+  return n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes && conv_shape(n_out, pairs, K3, c_in, c_out, dtype).fn;
 }
 
 hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
-                             int64_t mt_stride, const uint32_t* perm, int K3, void* y, const void* residual, int relu,
-                             int64_t n_out, int c_in, int c_out, int dtype, hipStream_t s) {
+                             int64_t mt_stride, const uint32_t* perm, int64_t pairs, int K3, void* y,
+                             const void* residual, int relu, int64_t n_out, int c_in, int c_out, int dtype,
+                             hipStream_t s) {
   if (n_out <= 0) return hipSuccess;
-  const ConvShape sh = conv_shape(n_out, K3, c_in, c_out, dtype);
+  const ConvShape sh = conv_shape(n_out, pairs, K3, c_in, c_out, dtype);
   if (!sh.fn || n_out >= ((int64_t)1 << 31) - 1024) return hipErrorInvalidValue;
   ProfScope ps(KN_CONV_SMALL, s);
   ConvArgs g;

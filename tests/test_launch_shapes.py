@@ -1,5 +1,5 @@
 """Host-side rules that shape launches: column tiles and rows per tile of the full-width
-matrix product.  No GPU: the rules take the card's sizes as arguments."""
+matrix product, and which layers run as one kernel.  No GPU: the rules take the card's sizes as arguments."""
 import ctypes
 
 import pytest
@@ -67,3 +67,52 @@ def test_float32_full_width_pads_a_third_at_most(c_in, wide):
     gemm_wide = B.lib()._ZN3spc9gemm_wideEiiii
     gemm_wide.restype = ctypes.c_bool
     assert gemm_wide(c_in, 64, B.SPCONV_F32, B.SPCONV_F32) == wide
+
+
+F32, F16, BF16 = B.SPCONV_F32, B.SPCONV_F16, B.SPCONV_BF16
+
+
+@pytest.mark.parametrize("n_out,per_out,K,c_in,c_out,dtype,one", [
+    (60_000, 2.9, 3, 32, 64, F16, True),        # 108 KiB of weights
+    (60_000, 2.9, 3, 48, 48, F16, False),       # 162 KiB
+    (60_000, 2.9, 3, 64, 32, BF16, True),
+    (60_000, 2.9, 3, 64, 48, F16, False),
+    (60_000, 6.8, 5, 8, 64, F16, True),
+    (60_000, 6.8, 5, 8, 96, F16, False),
+    (60_000, 1.0, 2, 96, 96, F16, True),
+    (60_000, 2.9, 3, 64, 16, F16, True),        # two k-steps, one tile
+    (60_000, 2.9, 3, 96, 16, F16, False),       # three
+    (60_000, 1.0, 1, 128, 32, F16, False),      # one launch in separate steps as well
+    (60_000, 1.0, 1, 64, 16, F16, True),        # (not with one tile)
+    (60_000, 1.0, 1, 96, 32, F16, True),
+    (8191, 2.9, 3, 32, 64, F16, False),         # few outputs, 108 KiB
+    (8192, 2.9, 3, 32, 64, F16, True),
+    (8191, 4.0, 3, 32, 64, F16, True),
+    (500, 1.1, 3, 32, 32, F16, True),           # 54 KiB
+    (500, 1.0, 2, 64, 64, F16, True),           # 64 KiB
+    (500, 1.0, 2, 64, 96, F16, False),
+    (500, 1.0, 2, 64, 96, BF16, False),
+    (60_000, 2.9, 3, 16, 64, F32, True),
+    (60_000, 2.9, 3, 16, 96, F32, False),       # more than four k-steps x tiles
+    (60_000, 1.1, 3, 16, 64, F32, False),       # hardly any neighbours
+    (60_000, 2.9, 3, 32, 32, F32, False),       # two k-steps, sparse
+    (60_000, 4.0, 3, 32, 32, F32, True),
+    (60_000, 1.0, 2, 32, 32, F32, True),
+    (60_000, 1.0, 1, 64, 128, F32, True),
+    (2000, 1.1, 3, 16, 16, F32, True),
+    (2000, 1.1, 3, 16, 32, F32, False),         # few outputs, two tiles
+    (2000, 1.1, 3, 8, 32, F32, False),
+    (2000, 1.1, 3, 4, 32, F32, True),           # four offsets per step
+    (2000, 7.4, 3, 16, 32, F32, True),
+    (2000, 7.4, 3, 16, 48, F32, False),
+])
+def test_layers_that_run_as_one_kernel(n_out, per_out, K, c_in, c_out, dtype, one):
+    assert _one_kernel(n_out, n_out, int(n_out * per_out), K, c_in, c_out, dtype) == one
+
+
+def _one_kernel(n_in, n_out, pairs, K, c_in, c_out, dtype):
+    i64, c_int = ctypes.c_int64, ctypes.c_int
+    # bool spc::conv_small_applies(int64_t, int64_t, int64_t, int, int, int, int)
+    f = B.lib()._ZN3spc18conv_small_appliesEllliiii
+    f.restype = ctypes.c_bool
+    return f(i64(n_in), i64(n_out), i64(pairs), c_int(K ** 3), c_int(c_in), c_int(c_out), c_int(dtype))
