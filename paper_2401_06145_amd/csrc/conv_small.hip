@@ -519,7 +519,9 @@ ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, 
 }  // namespace
 
 bool conv_small_applies(int64_t n_in, int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
-  return n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes && conv_shape(n_out, pairs, K3, c_in, c_out, dtype).fn;
+  // (positions up to two rounds of blocks past the last output are held in 32 bits)
+  return n_out < ((int64_t)1 << 31) - (1 << 16) && n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes &&
+         conv_shape(n_out, pairs, K3, c_in, c_out, dtype).fn;
 }
 
 hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
@@ -527,8 +529,8 @@ hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const i
                              const void* residual, int relu, int64_t n_out, int c_in, int c_out, int dtype,
                              hipStream_t s) {
   if (n_out <= 0) return hipSuccess;
+  if (!conv_small_applies(n_in, n_out, pairs, K3, c_in, c_out, dtype)) return hipErrorInvalidValue;
   const ConvShape sh = conv_shape(n_out, pairs, K3, c_in, c_out, dtype);
-  if (!sh.fn || n_out >= ((int64_t)1 << 31) - 1024) return hipErrorInvalidValue;
   ProfScope ps(KN_CONV_SMALL, s);
   ConvArgs g;
   g.x = x;

@@ -110,6 +110,16 @@ def test_layers_that_run_as_one_kernel(n_out, per_out, K, c_in, c_out, dtype, on
     assert _one_kernel(n_out, n_out, int(n_out * per_out), K, c_in, c_out, dtype) == one
 
 
+def test_one_kernel_positions_stay_in_32_bits():
+    """A transposed K = 1 map may have close to 2^31 outputs; positions past the last output
+    that the kernel looks ahead to must not wrap."""
+    assert _one_kernel(1000, 2 ** 31 - 2 ** 17, 1000, 1, 16, 16, F16)
+    assert not _one_kernel(1000, 2 ** 31 - 2 ** 15, 1000, 1, 16, 16, F16)
+    # input rows are addressed in 32 bits below the offset that stands for none
+    assert _one_kernel(7 * 2 ** 26, 1000, 1000, 1, 8, 16, F32) is False
+    assert _one_kernel(7 * 2 ** 24, 1000, 1000, 1, 8, 16, F32)
+
+
 def _one_kernel(n_in, n_out, pairs, K, c_in, c_out, dtype):
     i64, c_int = ctypes.c_int64, ctypes.c_int
     # bool spc::conv_small_applies(int64_t, int64_t, int64_t, int, int, int, int)
