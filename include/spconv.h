@@ -217,7 +217,7 @@ size_t spconv_forward_workspace_bytes(const spconv_map* m, int c_in, int c_out, 
  * forms GEMM partials: c_out 16, 32, 48, 64, 96 or 128, c_in up to 128 (float32 64), all
  * K^3 weight matrices in the LDS of a CU, inputs of at most 3.5 GiB, and of those the
  * layers that take less time that way, by their widths, outputs and pairs.  (K = 3, 16
- * bits: up to 32 -> 64, 64 -> 32 or 16 -> 128; float32 up to 16 -> 64, or 32 -> 32 from 4
+ * bits: up to 32 -> 64, 64 -> 32 or 16 -> 128; float32 up to 16 -> 64, or 32 -> 32 from 3.1
  * pairs per output.)  Results differ from the separate steps' by the rounding of partials.
  * An option that names a form of the separate steps (gather, centre, partial_dtype,
  * t_gather or t_scatter given) keeps them, and so does a d_y that overlaps d_x or d_w;

@@ -480,19 +480,20 @@ ConvShape conv_shape_k(int K3, int nt, int kpo, int gr) {
 //    48 and 64 -> 16, K = 3: 0.77 times their time over 60 layers).  K = 1 in 16 bits and widths
 //    that the centre scatter takes, one launch as well: kpo < 2 nt (128 -> 32, 179k voxels
 //    15.2 against 14.3 us);
-//  * 16 bits, under 512 blocks and 4 pairs per output: at most 64 KiB of weights, which
-//    every workgroup stages (500 voxels, K = 3, 32 -> 64 9.4 against 7.9 us, K = 2, 64 -> 128
-//    8.9 against 6.5; 54 KiB, K = 3, 32 -> 32, never over 1.02; with 7.4 pairs per output
-//    32 -> 64 never);
+//  * 16 bits, K = 2 or 3, under 512 blocks and 3.1 pairs per output: at most 64 KiB of
+//    weights, which every workgroup stages (500 voxels, K = 3, 32 -> 64 9.4 against 7.9 us,
+//    K = 2, 64 -> 128 8.9 against 6.5; 54 KiB, K = 3, 32 -> 32, never over 1.02; with 7.4 pairs
+//    per output 32 -> 64 never; K = 5, 32 -> 16 15.3 against 28.0: one offset's rows fill no
+//    tile of the separate steps, in two launches);
 //  * float32 (K > 1): kpo * nt <= 4, 2 under 512 blocks.  A block's products run in one
 //    wave, at every offset that any of its rows lists, and float32 MFMAs take twice the
 //    cycles for an eighth of the work: 64 -> 64, K = 2, 86k voxels 37.5 against 34.6 us.
-//    From K = 3 the separate steps, which multiply listed pairs only, win where few of a
-//    block's rows share an offset.  Under 4 pairs per output: kpo = 1 (32 -> 32, 120k LiDAR
+//    For K = 3 the separate steps, which multiply listed pairs only, win where few of a
+//    block's rows share an offset.  Under 3.1 pairs per output: kpo = 1 (32 -> 32, 120k LiDAR
 //    voxels 38.2 against 32.7 us, room down 70.9 against 51.7; at 5.6 pairs, 30k LiDAR 13.5
 //    against 22.9); under 512 blocks nt = 1 (16 -> 32, 2k voxels 9.1 against 8.3 us), or 2
-//    with four offsets per step; and under 1.2 pairs kpo * nt <= 3 (scattered voxels, stride
-//    2, 16 -> 64 35.4 against 30.8 us).
+//    with four offsets per step; and under 1.18 pairs kpo * nt <= 3 (scattered voxels, stride
+//    2, 16 -> 64 35.4 against 30.8 us; at 1.2 pairs, stride 1, 24.9 against 31.4).
 ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
   if (c_out % 16 != 0) return ConvShape{};
   const int ks = dtype == 0 ? 16 : 32;  // channels per k-step
@@ -501,14 +502,14 @@ ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, 
   if (gr > 1 && c_in * gr != ks) return ConvShape{};
   const int nt = c_out / 16;
   if (kpo > 2 * nt) return ConvShape{};
-  const bool few = n_out < 512 * 16, sparse = pairs < 4 * n_out;
+  const bool few = n_out < 512 * 16, sparse = 10 * pairs < 31 * n_out;
   if (dtype != 0) {
     if (K3 == 1 && c_out % 32 == 0 && kpo >= 2 * nt) return ConvShape{};
-    if (K3 > 1 && few && sparse && (K3 + gr - 1) / gr * kpo * nt > 64) return ConvShape{};
+    if (K3 > 1 && K3 <= 27 && few && sparse && (K3 + gr - 1) / gr * kpo * nt > 64) return ConvShape{};
   } else if (K3 > 1) {
     if (kpo * nt > (few ? 2 : 4)) return ConvShape{};
-    if (K3 >= 27 && sparse &&
-        (kpo > 1 || (few && nt > 1 && gr < 4) || (kpo * nt == 4 && gr == 1 && 5 * pairs < 6 * n_out)))
+    if (K3 == 27 && sparse &&
+        (kpo > 1 || (few && nt > 1 && gr < 4) || (kpo * nt == 4 && gr == 1 && 50 * pairs < 59 * n_out)))
       return ConvShape{};
   }
   if (dtype == 0) return conv_shape_k<float>(K3, nt, kpo, gr);

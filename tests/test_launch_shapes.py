@@ -87,7 +87,7 @@ F32, F16, BF16 = B.SPCONV_F32, B.SPCONV_F16, B.SPCONV_BF16
     (60_000, 1.0, 1, 96, 32, F16, True),
     (8191, 2.9, 3, 32, 64, F16, False),         # few outputs, 108 KiB
     (8192, 2.9, 3, 32, 64, F16, True),
-    (8191, 4.0, 3, 32, 64, F16, True),
+    (8191, 3.3, 3, 32, 64, F16, True),
     (500, 1.1, 3, 32, 32, F16, True),           # 54 KiB
     (500, 1.0, 2, 64, 64, F16, True),           # 64 KiB
     (500, 1.0, 2, 64, 96, F16, False),
@@ -96,7 +96,10 @@ F32, F16, BF16 = B.SPCONV_F32, B.SPCONV_F16, B.SPCONV_BF16
     (60_000, 2.9, 3, 16, 96, F32, False),       # more than four k-steps x tiles
     (60_000, 1.1, 3, 16, 64, F32, False),       # hardly any neighbours
     (60_000, 2.9, 3, 32, 32, F32, False),       # two k-steps, sparse
-    (60_000, 4.0, 3, 32, 32, F32, True),
+    (60_000, 3.3, 3, 32, 32, F32, True),
+    (500, 1.9, 5, 32, 16, F16, True),           # 125 offsets of few pairs
+    (500, 1.9, 5, 8, 32, F32, True),
+    (60_000, 1.2, 3, 16, 64, F32, True),
     (60_000, 1.0, 2, 32, 32, F32, True),
     (60_000, 1.0, 1, 64, 128, F32, True),
     (2000, 1.1, 3, 16, 16, F32, True),
