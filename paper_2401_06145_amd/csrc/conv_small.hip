@@ -299,27 +299,9 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
   __syncthreads();  // (s_bad is clear)
   if (__ballot(Finite<T>::exceeded(top)) != 0 && lane == 0) s_bad = 1;
   __syncthreads();
-  if (s_bad) {
-    // Rows without a pair would multiply a weight that is not finite by zero: plain
-    // sums over the pairs instead.
-    for (int blk = b0; blk < last; blk += bstride)
-      for (int p = blk * 16; p < min(blk * 16 + 16, g.n_out); ++p)
-        for (int n = lane; n < g.c_out; n += 64) {
-          float s = 0.f;
-          for (int k = 0; k < g.K3; ++k) {
-            const int32_t pr = g.omt[(int64_t)k * g.stride + p];
-            if (pr < 0) continue;
-            const T* xr_ = static_cast<const T*>(g.x) + (int64_t)g.pin[pr] * g.c_in;
-            const T* w = static_cast<const T*>(g.w) + (int64_t)k * g.c_in * g.c_out + n;
-            for (int c = 0; c < g.c_in; ++c) s = fmaf((float)xr_[c], (float)w[(int64_t)c * g.c_out], s);
-          }
-          const int64_t at = (g.perm ? (int64_t)g.perm[p] : (int64_t)p) * g.c_out + n;
-          if (g.residual) s += (float)static_cast<const T*>(g.residual)[at];
-          if (g.relu) s = fmaxf(s, 0.f);
-          static_cast<T*>(g.y)[at] = (T)s;
-        }
-    return;
-  }
+  // A row without a pair would multiply a weight that is not finite by zero: then each
+  // offset's products are summed by themselves and added to the rows that have a pair.
+  const bool bad = __builtin_amdgcn_readfirstlane(s_bad) != 0;
 
   T* y = static_cast<T*>(g.y);
   const T* res = static_cast<const T*>(g.residual);
@@ -328,29 +310,118 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
 #pragma unroll
   for (int q = 0; q < KPO; ++q) qoff[q] = (q * 4 + (G == 1 ? sub : sub % SPO)) * E < g.c_in ? q * 64 + (G == 1 ? sub * 16 : piece) : kNoRow;
 
+  // src's rows to the list, and the steps that have any
+  auto listed = [&]() {
+    uint32_t todo = 0;
+#pragma unroll
+    for (int m = 0; m < MG; ++m) {
+      list[64 * m + lane] = src[m];
+      const uint64_t b = __ballot(src[m] != kNoRow);
+      if constexpr (G == 4) {
+        todo |= b ? 1u << m : 0u;
+      } else if constexpr (G == 2) {
+        todo |= ((uint32_t)b ? 1u << (2 * m) : 0u) | ((uint32_t)(b >> 32) ? 2u << (2 * m) : 0u);
+      } else {
+        todo |= ((uint32_t)b & 0xFFFFu ? 1u << (4 * m) : 0u) | ((uint32_t)b >> 16 ? 2u << (4 * m) : 0u) |
+                ((uint32_t)(b >> 32) & 0xFFFFu ? 4u << (4 * m) : 0u) | (b >> 48 ? 8u << (4 * m) : 0u);
+      }
+    }
+    asm volatile("" ::: "memory");
+    return todo;
+  };
+  auto row_of = [&](int blk) {
+    const int p = min(blk * 16 + col, g.n_out - 1);
+    return g.perm ? (int64_t)g.perm[p] : (int64_t)p;
+  };
+  // each lane holds, for its row, columns 4 sub .. + 3 of every tile.  Plain stores: a
+  // store writes 64 bytes of each of 16 rows, parts of lines that the caches
+  // gather; non-temporal ones took 300k rows, K = 1, 48 -> 128 from 26.7 to 31.4 us, over 148
+  // layers with outputs of 64 MiB and more 1.11 times as long.
+  auto finish = [&](int blk, int64_t row, const f32x4* acc) {
+    if (blk * 16 + col < g.n_out) {
+      constexpr int W = Out<T>::N;  // channels per 16-byte vector
+      constexpr int TV = W / 4;     // tiles per vector
+      const int64_t at = row * g.c_out;
+#pragma unroll
+      for (int v = 0; v < NT / TV; ++v) {
+        const int64_t o = at + conv_channel<T>(NT, v * TV, 4 * sub);
+        float s[W];
+#pragma unroll
+        for (int t = 0; t < TV; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[4 * t + i] = acc[v * TV + t][i];
+        if (res) Out<T>::add(s, *reinterpret_cast<const u32x4*>(res + o));
+        if (g.relu) {
+#pragma unroll
+          for (int i = 0; i < W; ++i) s[i] = fmaxf(s[i], 0.f);
+        }
+        *reinterpret_cast<uint4*>(y + o) = Out<T>::pack(s);
+      }
+      if constexpr (NT % TV != 0) {  // the last tile of an odd count: 4 channels, 8 bytes
+        const int64_t o = at + 16 * (NT - 1) + 4 * sub;
+        float s[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) s[i] = i < 4 ? acc[NT - 1][i] : 0.f;
+        if (res) {
+          const uint2 rv = *reinterpret_cast<const uint2*>(res + o);
+          Out<T>::add(s, u32x4{rv.x, rv.y, 0, 0});
+        }
+        if (g.relu) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[i] = fmaxf(s[i], 0.f);
+        }
+        const uint4 out = Out<T>::pack(s);
+        *reinterpret_cast<uint2*>(y + o) = make_uint2(out.x, out.y);
+      }
+    }
+  };
+
+  if (bad) {
+    for (int blk = b0; blk < last; blk += bstride) {
+      f32x4 acc[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int grp = 0; grp < groups; ++grp) {
+        table(blk, grp, e);
+        rows_of(e, src);
+        for (uint32_t todo = listed(); todo; todo &= todo - 1) {
+          const int s = __builtin_ctz(todo);
+          const u32x4* wp = sw + (grp * (kOffsetGroup / G) + s) * (KPO * NT * 64) + lane;
+#pragma nounroll
+          for (int o = 0; o < G; ++o) {
+            // the step's o-th offset; zeros in the other offsets' lanes of both operands
+            const uint32_t off = list[(s * G + o) * 16 + col];
+            const uint32_t mine = sub / SPO == o ? 0xFFFFFFFFu : 0u;
+            u32x4 a[KPO];
+#pragma unroll
+            for (int q = 0; q < KPO; ++q) {
+              const uint32_t at = (off == kNoRow || qoff[q] == kNoRow) ? kNoRow : off + qoff[q];
+              a[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)at, 0, 0)) & mine;
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              asm volatile("" ::: "memory");  // one tile's weights at a time (all ahead they spill)
+              f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int q = 0; q < KPO; ++q) part = M::mma(wp[(q * NT + t) * 64] & mine, a[q], part);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) acc[t][j] += off != kNoRow ? part[j] : 0.f;
+            }
+          }
+        }
+      }
+      finish(blk, row_of(blk), acc);
+    }
+    return;
+  }
+
   for (int blk = b0; blk < last; blk += bstride) {
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int p = blk * 16 + col;
-    const int64_t row = g.perm ? (int64_t)g.perm[min(p, g.n_out - 1)] : (int64_t)p;
+    const int64_t row = row_of(blk);
     for (int grp = 0; grp < groups; ++grp) {
-      // the unit's rows to the list, and the steps that have any
-      uint32_t todo = 0;
-#pragma unroll
-      for (int m = 0; m < MG; ++m) {
-        list[64 * m + lane] = src[m];
-        const uint64_t b = __ballot(src[m] != kNoRow);
-        if constexpr (G == 4) {
-          todo |= b ? 1u << m : 0u;
-        } else if constexpr (G == 2) {
-          todo |= ((uint32_t)b ? 1u << (2 * m) : 0u) | ((uint32_t)(b >> 32) ? 2u << (2 * m) : 0u);
-        } else {
-          todo |= ((uint32_t)b & 0xFFFFu ? 1u << (4 * m) : 0u) | ((uint32_t)b >> 16 ? 2u << (4 * m) : 0u) |
-                  ((uint32_t)(b >> 32) & 0xFFFFu ? 4u << (4 * m) : 0u) | (b >> 48 ? 8u << (4 * m) : 0u);
-        }
-      }
-      asm volatile("" ::: "memory");
+      uint32_t todo = listed();
       rows_of(e, src);  // of the next unit
       table(nb, ng, e);
       advance();
@@ -402,46 +473,7 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
         }
       }
     }
-    // each lane holds, for its row, columns 4 sub .. + 3 of every tile.  Plain stores: a
-    // store writes 64 bytes of each of 16 rows, parts of lines that the caches
-    // gather; non-temporal ones took 300k rows, K = 1, 48 -> 128 from 26.7 to 31.4 us, over 148
-    // layers with outputs of 64 MiB and more 1.11 times as long.
-    if (p < g.n_out) {
-      constexpr int W = Out<T>::N;  // channels per 16-byte vector
-      constexpr int TV = W / 4;     // tiles per vector
-      const int64_t at = row * g.c_out;
-#pragma unroll
-      for (int v = 0; v < NT / TV; ++v) {
-        const int64_t o = at + conv_channel<T>(NT, v * TV, 4 * sub);
-        float s[W];
-#pragma unroll
-        for (int t = 0; t < TV; ++t)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[4 * t + i] = acc[v * TV + t][i];
-        if (res) Out<T>::add(s, *reinterpret_cast<const u32x4*>(res + o));
-        if (g.relu) {
-#pragma unroll
-          for (int i = 0; i < W; ++i) s[i] = fmaxf(s[i], 0.f);
-        }
-        *reinterpret_cast<uint4*>(y + o) = Out<T>::pack(s);
-      }
-      if constexpr (NT % TV != 0) {  // the last tile of an odd count: 4 channels, 8 bytes
-        const int64_t o = at + 16 * (NT - 1) + 4 * sub;
-        float s[W];
-#pragma unroll
-        for (int i = 0; i < W; ++i) s[i] = i < 4 ? acc[NT - 1][i] : 0.f;
-        if (res) {
-          const uint2 rv = *reinterpret_cast<const uint2*>(res + o);
-          Out<T>::add(s, u32x4{rv.x, rv.y, 0, 0});
-        }
-        if (g.relu) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[i] = fmaxf(s[i], 0.f);
-        }
-        const uint4 out = Out<T>::pack(s);
-        *reinterpret_cast<uint2*>(y + o) = make_uint2(out.x, out.y);
-      }
-    }
+    finish(blk, row, acc);
   }
 }
 

@@ -72,3 +72,17 @@ def elem_err(y: np.ndarray, ref: np.ndarray) -> float:
 
 def features_f64(a: np.ndarray, dtype: str) -> np.ndarray:
     return scenes.to_f64(a, dtype)
+
+
+def forward_kernels(fn) -> dict:
+    """The forward kernels that fn() launches, by the library's own counters: name -> launches."""
+    torch.cuda.synchronize()
+    B.spconv_profile_read(reset=True)
+    B.spconv_profile_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+    finally:
+        B.spconv_profile_enable(False)
+    got = B.spconv_profile_read(reset=True)
+    return {k: got[k][1] for k in ("k_gather", "k_gemm", "k_scatter", "k_scatter_centre", "k_conv_small") if got[k][1]}
