@@ -23,7 +23,6 @@
 // offsets at a time with two row blocks per wave (even at 64 and 128 channels, twice
 // the time at 256).
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "common.h"
@@ -202,7 +201,7 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
   const int bstride = ((int)gridDim.x >> 3) * kConvWaves;
   const int b0 = first + wave * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);  // small clouds use all workgroups
 
-  // Units: (block, group of 28 offsets).  A unit's table entries are requested two
+  // Units: (block, group of 28 offsets, 8 for K <= 2).  A unit's table entries are requested two
   // units ahead, their pairs' input rows one ahead.
   const int groups = (g.K3 + kOffsetGroup - 1) / kOffsetGroup;
   auto table = [&](int blk, int grp, int32_t* e) {
@@ -484,12 +483,19 @@ struct ConvShape {
 
 constexpr size_t kConvLdsMax = 160 * 1024 - 64;
 
+// Widths and offsets that an instance serves (the reasons stand with the rule below).
+constexpr bool conv_fits(int elem, int K3, int nt, int kpo, int g, int mg) {
+  return kpo <= 2 * nt && (elem == 2 || K3 == 1 || kpo * nt <= 4) && conv_lds(K3, nt, kpo, g, mg) <= kConvLdsMax;
+}
+
 template <typename T, int MG>
 ConvShape conv_shape_t(int K3, int nt, int kpo, int gr) {
-  const size_t lds = conv_lds(K3, nt, kpo, gr, MG);
-  if (lds > kConvLdsMax) return ConvShape{};
-#define SPC_V(N, Q, G_) \
-  if (nt == N && kpo == Q && gr == G_) return ConvShape{reinterpret_cast<const void*>(&k_conv_small<T, N, Q, G_, MG>), lds};
+  constexpr int kLeast = MG == 2 ? 1 : 27;  // the fewest offsets with this many entries per lane
+  if (!conv_fits((int)sizeof(T), K3, nt, kpo, gr, MG)) return ConvShape{};
+#define SPC_V(N, Q, G_)                                                   \
+  if constexpr (conv_fits((int)sizeof(T), kLeast, N, Q, G_, MG))          \
+    if (nt == N && kpo == Q && gr == G_)                                  \
+      return ConvShape{reinterpret_cast<const void*>(&k_conv_small<T, N, Q, G_, MG>), conv_lds(K3, nt, kpo, gr, MG)};
 #define SPC_VN(N) SPC_V(N, 1, 1) SPC_V(N, 1, 2) SPC_V(N, 1, 4) SPC_V(N, 2, 1) SPC_V(N, 3, 1) SPC_V(N, 4, 1)
   SPC_VN(1) SPC_VN(2) SPC_VN(3) SPC_VN(4) SPC_VN(6) SPC_VN(8)
 #undef SPC_VN
@@ -533,13 +539,12 @@ ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, 
   const int kpo = gr > 1 ? 1 : (c_in + ks - 1) / ks;
   if (gr > 1 && c_in * gr != ks) return ConvShape{};
   const int nt = c_out / 16;
-  if (kpo > 2 * nt) return ConvShape{};
   const bool few = n_out < 512 * 16, sparse = 10 * pairs < 31 * n_out;
   if (dtype != 0) {
     if (K3 == 1 && c_out % 32 == 0 && kpo >= 2 * nt) return ConvShape{};
     if (K3 > 1 && K3 <= 27 && few && sparse && (K3 + gr - 1) / gr * kpo * nt > 64) return ConvShape{};
   } else if (K3 > 1) {
-    if (kpo * nt > (few ? 2 : 4)) return ConvShape{};
+    if (few && kpo * nt > 2) return ConvShape{};
     if (K3 == 27 && sparse &&
         (kpo > 1 || (few && nt > 1 && gr < 4) || (kpo * nt == 4 && gr == 1 && 50 * pairs < 59 * n_out)))
       return ConvShape{};

@@ -962,8 +962,11 @@ int wide_ksteps(int c_in, int elem) {
   return 0;
 }
 
-// Instantiated (NT, KSTEPS) pairs: the W^T slice fits the LDS.
-constexpr bool wide_fits(int nt, int ks) { return wide_lds(nt, ks) <= kLdsMax; }
+// Instantiated (NT, KSTEPS) pairs: the W^T slice fits the LDS, and float32's unrolled
+// products the registers.
+constexpr bool wide_fits(int nt, int ks, int elem) {
+  return wide_lds(nt, ks) <= kLdsMax && !(elem == 4 && nt == 16 && ks > 4);
+}
 
 // Column tiles per workgroup for the wide kernel: the widest instantiated divisor
 // of c_out / 16 whose W^T slice fits the LDS; 0 if the wide kernel does not apply.
@@ -978,10 +981,8 @@ int wide_nt(int c_in, int c_out, int elem) {
   // over 1.05; 12 and 20 channels 0.93 and 0.92, up to 1.19; 16 and 36 0.91 and 0.86.
   if (elem == 4 && (c_in < 16 || 16 * ks * 3 > 4 * c_in)) return 0;
   const int nt_all = c_out / 16;
-  for (int nt : {16, 12, 8, 6, 4, 3, 2, 1}) {
-    if (elem == 4 && nt == 16 && ks > 4) continue;  // (float32: the unrolled products spill)
-    if (nt_all % nt == 0 && wide_fits(nt, ks)) return nt;
-  }
+  for (int nt : {16, 12, 8, 6, 4, 3, 2, 1})
+    if (nt_all % nt == 0 && wide_fits(nt, ks, elem)) return nt;
   return 0;
 }
 
@@ -991,7 +992,7 @@ int wide_round_rows(int nt, int ks, int elem) { return kWideWaves / wide_cg(nt) 
 template <typename T, typename TO, bool GATHER>
 const void* wide_kernel(int nt, int ks) {
 #define SPC_W(N, KS_)                                                                                     \
-  if constexpr (wide_fits(N, KS_)) {                                                                       \
+  if constexpr (wide_fits(N, KS_, (int)sizeof(T))) {                                                                       \
     if (nt == N && ks == KS_) return reinterpret_cast<const void*>(&k_gemm_wide<T, TO, N, KS_, GATHER>); \
   }
 #define SPC_WK(N) \
