@@ -14,7 +14,8 @@
 * ``unet``: Algorithm 2 per layer over the UNet-style network's convolutions (the
   two-scene batch): the Scatter tile, the GEMM's rows per workgroup tile and, for
   Algorithm 1's gather kernel (the buffer form), the Gather tile; then the whole
-  forward with the per-layer winners against the constant defaults.
+  forward with the per-layer winners against the constant defaults.  These shape the
+  separate steps; layers that run as one kernel keep the defaults.
 
 Timings are HIP-event means recorded by the library on the launch stream.
 Prints one JSON object per measured point and, at the end, the selection.
@@ -50,7 +51,20 @@ def _timed(fn, kernel: str, rounds: int) -> float:
     torch.cuda.synchronize()
     B.spconv_profile_enable(False)
     ms, cnt = B.spconv_profile_read(reset=True)[kernel]
-    return ms / max(cnt, 1)
+    if cnt == 0:
+        raise RuntimeError(f"{kernel} was not launched")
+    return ms / cnt
+
+
+def _launches(fn, kernel: str) -> bool:
+    """Whether fn launches the kernel."""
+    torch.cuda.synchronize()
+    B.spconv_profile_read(reset=True)
+    B.spconv_profile_enable(1 << B.profile_ids()[kernel])
+    fn()
+    torch.cuda.synchronize()
+    B.spconv_profile_enable(False)
+    return B.spconv_profile_read(reset=True)[kernel][1] > 0
 
 
 def tile_candidates(c: int, elem: int, max_vectors: int = 16):
@@ -148,7 +162,43 @@ def tune_map(workloads, rounds: int, Bs, Cqs, wgs=(256,)):
     return best
 
 
-def tune_unet(rounds: int, rows_cands=(64, 128, 256, 512, 1024, 2048, 4096), forward_steps: int = 20):
+ROWS_CANDS = (64, 128, 256, 512, 1024, 2048, 4096)
+
+
+def tune_layer(km, op, x, w, res, rounds: int, rows_cands=ROWS_CANDS) -> dict:
+    """Algorithm 2 for one 16-bit layer of a network: its tiles' times and the fastest of
+    each.  The candidates name the separate steps, so that they are what is timed."""
+    def run(kernel, **opt):
+        f = B.Forward(km, op.c_in, op.c_out, x.dtype, B.Options.make(**opt))
+        return _timed(lambda: f(x, w, residual=res, relu=op.relu), kernel, rounds)
+
+    f = B.Forward(km, op.c_in, op.c_out, x.dtype)
+    one_kernel = _launches(lambda: f(x, w, residual=res, relu=op.relu), "k_conv_small")
+    sc = {t: run("k_scatter", t_scatter=t, centre=1)
+          for t in tile_candidates(op.c_out, 2) if 8 <= t <= 64 and (t & (t - 1)) == 0}
+    # (a K = 1 layer whose only offset is multiplied inside the scatter has no GEMM)
+    gm = {r: run("k_gemm", gemm_tile_rows=r, gather=B.GATHER_FUSED)
+          for r in (0, *rows_cands)} if f.plan.n_gemm_launches else {0: 0.0}
+    # Algorithm 1's kernel takes tiles of 1, 2, 4, 8 or 16 16-byte vectors
+    ga = {t: run("k_gather", t_gather=t, gather=B.GATHER_BUFFER)
+          for t in tile_candidates(op.c_in, 2) if (t // 8) & (t // 8 - 1) == 0}
+    return {"layer": op.out, "mode": op.mode, "K": op.K, "level": op.level, "n_out": km.n_out,
+            "pairs": sum(km.counts()), "c_in": op.c_in, "c_out": op.c_out, "one_kernel": one_kernel,
+            "scatter_us": {t: round(v * 1e3, 2) for t, v in sc.items()},
+            "gemm_us": {r: round(v * 1e3, 2) for r, v in gm.items()},
+            "gather_us": {t: round(v * 1e3, 2) for t, v in ga.items()},
+            "t_scatter": min(sc, key=sc.get), "gemm_tile_rows": min(gm, key=gm.get),
+            "t_gather": min(ga, key=ga.get)}
+
+
+def tuned_options(table: dict) -> dict:
+    """Per-layer options of a tuned table (layer name -> row of tune_layer).  A scatter tile
+    takes a layer off the one-kernel form: layers that run as one kernel have no entry."""
+    return {k: B.Options.make(t_scatter=v["t_scatter"], gemm_tile_rows=v["gemm_tile_rows"])
+            for k, v in table.items() if not v["one_kernel"]}
+
+
+def tune_unet(rounds: int, rows_cands=ROWS_CANDS, forward_steps: int = 20):
     """Algorithm 2 per layer of the UNet-style network, then the forward with the
     winners against the defaults.  Returns the per-layer table."""
     import time
@@ -169,27 +219,8 @@ def tune_unet(rounds: int, rows_cands=(64, 128, 256, 512, 1024, 2048, 4096), for
         km = model._map(op.level, op.K, op.mode)
         x = torch.randn(km.n_in, op.c_in, device=dev).to(torch.float16)
         res = torch.randn(km.n_out, op.c_out, device=dev).to(torch.float16) if op.residual else None
-        w = weights[op.out]
-
-        def run(opt, kernel):
-            f = B.Forward(km, op.c_in, op.c_out, torch.float16, opt)
-            return _timed(lambda: f(x, w, residual=res, relu=op.relu), kernel, rounds)
-
-        sc = {t: run(B.Options.make(t_scatter=t, centre=1), "k_scatter")
-              for t in tile_candidates(op.c_out, 2) if 8 <= t <= 64 and (t & (t - 1)) == 0}
-        gm = {r: run(B.Options.make(gemm_tile_rows=r), "k_gemm") for r in (0, *rows_cands)}
-        # Algorithm 1's kernel takes tiles of 1, 2, 4, 8 or 16 16-byte vectors
-        ga = {t: run(B.Options.make(t_gather=t, gather=B.GATHER_BUFFER), "k_gather")
-              for t in tile_candidates(op.c_in, 2) if (t // 8) & (t // 8 - 1) == 0}
-        row = {"layer": op.out, "mode": op.mode, "K": op.K, "level": op.level, "n_out": km.n_out,
-               "pairs": sum(km.counts()), "c_in": op.c_in, "c_out": op.c_out,
-               "scatter_us": {t: round(v * 1e3, 2) for t, v in sc.items()},
-               "gemm_us": {r: round(v * 1e3, 2) for r, v in gm.items()},
-               "gather_us": {t: round(v * 1e3, 2) for t, v in ga.items()},
-               "t_scatter": min(sc, key=sc.get), "gemm_tile_rows": min(gm, key=gm.get),
-               "t_gather": min(ga, key=ga.get)}
+        table[op.out] = row = tune_layer(km, op, x, weights[op.out], res, rounds, rows_cands)
         print(json.dumps(row), flush=True)
-        table[op.out] = row
 
     def forward_ms(layer_opts):
         m = net.UNet(coords, ops=ops, weights=weights, layer_opts=layer_opts)
@@ -204,7 +235,7 @@ def tune_unet(rounds: int, rows_cands=(64, 128, 256, 512, 1024, 2048, 4096), for
         _ = m
         return (time.perf_counter() - t0) * 1e3 / forward_steps
 
-    tuned = {k: B.Options.make(t_scatter=v["t_scatter"], gemm_tile_rows=v["gemm_tile_rows"]) for k, v in table.items()}
+    tuned = tuned_options(table)
     res = []
     for _ in range(3):  # alternate, so drift hits both
         res.append((forward_ms(None), forward_ms(tuned)))
