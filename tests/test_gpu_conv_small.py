@@ -22,10 +22,7 @@ ROUNDING = {"f32": TOL["f32"], "f16": 2.0 ** -11 * 1.05, "bf16": 2.0 ** -8 * 1.0
 
 
 def _cloud(seed, n, side):
-    rng = np.random.default_rng(seed)
-    cells = rng.choice(side ** 3, n, replace=False)
-    c = np.stack([np.zeros(n), cells // side ** 2, cells // side % side, cells % side], 1).astype(np.int32)
-    return np.ascontiguousarray(c)
+    return scenes.uniform_cells(n, side, seed)
 
 
 def _layer(K, c_in, c_out, dtype, coords, mode="subm", seed=1):
@@ -43,35 +40,20 @@ def _layer(K, c_in, c_out, dtype, coords, mode="subm", seed=1):
     return km, okm, x, w, ref
 
 
-@pytest.mark.parametrize("dtype,K,c_in,c_out,mode,n", [
-    ("f16", 3, 32, 32, "subm", 1),        # one row
-    ("f16", 3, 32, 64, "subm", 16),       # one block
-    ("f16", 3, 48, 32, "subm", 17),       # two k-steps, the second half empty; a block and a row
-    ("bf16", 3, 16, 48, "subm", 127),     # two offsets per k-step; odd tiles; eight dies less one block
-    ("bf16", 3, 8, 16, "subm", 2049),     # four offsets per k-step, one tile
-    ("f16", 5, 8, 32, "subm", 3001),      # 125 offsets: five groups, the last of 13
-    ("f16", 2, 24, 96, "subm", 3000),     # eight offsets: two entries per lane; a quarter k-step empty
-    ("f16", 1, 64, 128, "subm", 3000),
-    ("f16", 2, 96, 96, "up", 3000),       # three k-steps
-    ("bf16", 2, 64, 128, "down", 3000),
-    ("bf16", 3, 32, 64, "down", 3000),
-    ("f32", 3, 16, 16, "subm", 3000),
-    ("f32", 3, 4, 32, "subm", 3000),      # four offsets per k-step
-    ("f32", 3, 8, 16, "up", 3000),
-    ("f32", 3, 32, 32, "subm", 9000),
-    ("f32", 1, 48, 96, "subm", 500),
-])
-def test_narrow_layer_matches_oracle(dtype, K, c_in, c_out, mode, n):
-    say(f"one-kernel layer {dtype} K={K} {c_in}->{c_out} {mode} n={n}")
-    coords = _cloud(900 + n + K, n, 40 if n > 5000 else 16)
+def _check(dtype, K, c_in, c_out, mode, n, side, one):
+    """Parity of the default form, which is one kernel or not, and of the separate steps."""
+    coords = _cloud(900 + n + K, n, side)
     km, _, x, w, ref = _layer(K, c_in, c_out, dtype, coords, mode)
     f = B.Forward(km, c_in, c_out, B.TORCH_DTYPES[dtype])
     xd, wd = to_dev(x, dtype), to_dev(w, dtype)
+    assert (forward_kernels(lambda: f(xd, wd)) == {"k_conv_small": 1}) == one
     y = f(xd, wd)
-    assert rel_err(to_f64(y), ref) <= ROUNDING[dtype]
+    assert rel_err(to_f64(y), ref) <= (ROUNDING if one else TOL)[dtype]
     assert torch.equal(f(xd, wd), y)  # repeatable bit for bit
     # the separate steps (named by an option) stay within the common tolerance of it
-    sep = B.Forward(km, c_in, c_out, B.TORCH_DTYPES[dtype], B.Options.make(gather=B.GATHER_FUSED))(xd, wd)
+    fs = B.Forward(km, c_in, c_out, B.TORCH_DTYPES[dtype], B.Options.make(gather=B.GATHER_FUSED))
+    assert "k_conv_small" not in forward_kernels(lambda: fs(xd, wd))
+    sep = fs(xd, wd)
     assert rel_err(to_f64(sep), to_f64(y)) <= TOL[dtype]
     if dtype == "f32" and n >= 2000:
         # both sum an offset's channels first and then the offsets, so their errors differ
@@ -80,7 +62,76 @@ def test_narrow_layer_matches_oracle(dtype, K, c_in, c_out, mode, n):
         assert np.linalg.norm(to_f64(y) - ref) <= 1.25 * np.linalg.norm(to_f64(sep) - ref)
     res = scenes.features(km.n_out, c_out, dtype, 7)
     ye = f(xd, wd, residual=to_dev(res, dtype), relu=True)
-    assert rel_err(to_f64(ye), np.maximum(ref + scenes.to_f64(res, dtype), 0.0)) <= 2 * ROUNDING[dtype]
+    assert rel_err(to_f64(ye), np.maximum(ref + scenes.to_f64(res, dtype), 0.0)) <= \
+        2 * (ROUNDING if one else TOL)[dtype]
+
+
+@pytest.mark.parametrize("dtype,K,c_in,c_out,mode,n,one", [
+    ("f16", 3, 32, 32, "subm", 1, True),        # one row
+    ("f16", 3, 32, 64, "subm", 16, False),      # few outputs, sparse, 108 KiB of weights
+    ("f16", 3, 48, 32, "subm", 17, False),
+    ("bf16", 3, 16, 48, "subm", 127, True),     # two offsets per k-step; odd tiles; eight dies less one block
+    ("bf16", 3, 8, 16, "subm", 2049, True),     # four offsets per k-step, one tile
+    ("f16", 5, 8, 32, "subm", 3001, True),      # 125 offsets: five groups, the last of 13
+    ("f16", 2, 24, 96, "subm", 3000, True),     # eight offsets: two entries per lane; a quarter k-step empty
+    ("f16", 1, 64, 128, "subm", 3000, True),
+    ("f16", 2, 96, 96, "up", 3000, False),
+    ("bf16", 2, 64, 128, "down", 3000, True),   # (dense: eight inputs per output)
+    ("bf16", 3, 32, 64, "down", 3000, True),
+    ("f32", 3, 16, 16, "subm", 3000, True),
+    ("f32", 3, 4, 32, "subm", 3000, True),      # four offsets per k-step
+    ("f32", 3, 8, 16, "up", 3000, True),
+    ("f32", 3, 32, 32, "subm", 9000, True),
+    ("f32", 1, 48, 96, "subm", 500, True),
+])
+def test_narrow_layer_matches_oracle(dtype, K, c_in, c_out, mode, n, one):
+    say(f"narrow layer {dtype} K={K} {c_in}->{c_out} {mode} n={n}")
+    _check(dtype, K, c_in, c_out, mode, n, 40 if n > 5000 else 16, one)
+
+
+@pytest.mark.parametrize("dtype,K,c_in,c_out,mode,n,side,one", [
+    ("f16", 3, 32, 64, "subm", 16, 3, True),       # one block
+    ("f16", 3, 48, 32, "subm", 17, 3, True),       # two k-steps, the second half empty; a block and a row
+    ("f16", 2, 96, 96, "up", 9000, 40, True),      # three k-steps
+    ("bf16", 2, 64, 128, "down", 20000, 60, True),
+    ("f16", 3, 48, 48, "subm", 9000, 40, False),   # the first width past the LDS
+    ("f16", 4, 32, 16, "subm", 3000, 16, True),    # 64 offsets: three groups, the last of 8
+    ("bf16", 4, 16, 48, "subm", 3000, 24, True),   # the same, two offsets per step
+    ("f32", 4, 16, 16, "down", 3000, 16, True),
+    ("f16", 5, 16, 32, "subm", 3000, 24, True),    # several groups, two offsets per step
+    ("bf16", 5, 32, 16, "down", 3000, 24, True),   # one
+    ("f32", 5, 4, 32, "subm", 3000, 16, True),     # four
+    ("f32", 5, 8, 16, "subm", 3000, 24, True),
+    ("f32", 2, 32, 32, "up", 9000, 40, True),
+    ("f32", 3, 16, 64, "subm", 9000, 40, True),
+])
+def test_narrow_layer_groups_and_limits(dtype, K, c_in, c_out, mode, n, side, one):
+    say(f"narrow layer {dtype} K={K} {c_in}->{c_out} {mode} n={n} in {side}^3")
+    _check(dtype, K, c_in, c_out, mode, n, side, one)
+
+
+@pytest.mark.parametrize("dtype,K,c_in", [("f16", 3, 24), ("bf16", 3, 48), ("f16", 3, 16), ("bf16", 3, 8), ("f16", 2, 96),
+                                          ("f32", 3, 16), ("f32", 3, 8), ("f32", 3, 4), ("f32", 2, 12)])
+def test_an_input_row_that_is_not_finite(dtype, K, c_in):
+    """An infinite input row reaches the outputs that have a pair with it, and no others:
+    they keep their bits.  One, two and four offsets per k-step, k-steps that are part empty."""
+    say(f"non-finite input {dtype} K={K} c_in={c_in}")
+    coords = _cloud(81, 3000, 16)
+    km, okm, x, w, _ = _layer(K, c_in, 32, dtype, coords)
+    f = B.Forward(km, c_in, 32, B.TORCH_DTYPES[dtype])
+    xd, wd = to_dev(x, dtype), to_dev(w, dtype)
+    y0 = f(xd, wd)
+    xd[1234] = float("inf")
+    assert forward_kernels(lambda: f(xd, wd)) == {"k_conv_small": 1}
+    y = f(xd, wd)
+    reached = np.zeros(len(coords), dtype=bool)
+    for k in range(okm.K3):
+        a, b = okm.pairs(k)
+        reached[b[a == 1234]] = True
+    assert 0 < reached.sum() < len(coords)
+    r = torch.from_numpy(reached).to(y.device)
+    assert torch.equal(y[~r], y0[~r])
+    assert not torch.isfinite(y[r]).all(dim=1).any()
 
 
 @pytest.mark.parametrize("dtype,c_in", [("f16", 32), ("bf16", 16), ("f32", 16)])
@@ -114,8 +165,39 @@ def test_output_over_the_input():
     km, _, x, w, ref = _layer(3, 16, 16, "f32", coords)
     xd, wd = to_dev(x), to_dev(w)
     f = B.Forward(km, 16, 16, torch.float32)
+    xs = xd.clone()
+    assert "k_conv_small" not in forward_kernels(lambda: f(xs, wd, y=xs))
     assert f(xd, wd, y=xd) is xd
     assert rel_err(to_f64(xd), ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("what,shift", [("x", 4), ("x", -1000), ("x", 47_996), ("w", 0), ("w", 6_908), ("w", -47_996)])
+def test_output_over_part_of_an_operand(what, shift):
+    """The same for an output that begins or ends inside the input or the weights; one that
+    only touches them runs as one kernel."""
+    say(f"output over part of {what}, {shift} elements on")
+    n = 3000
+    coords = _cloud(82, n, 16)
+    km, _, x, w, ref = _layer(3, 16, 16, "f32", coords)
+    f = B.Forward(km, 16, 16, torch.float32)
+    buf = torch.empty(4 * 16 * n, device="cuda")
+    at = 16 * n  # of the operand; the output lies `shift` elements on
+    op = to_dev(x if what == "x" else w)
+    held = buf[at:at + op.numel()].view(op.shape)
+    y = buf[at + shift:at + shift + 16 * n].view(n, 16)
+    other = to_dev(w if what == "x" else x)
+
+    def run():
+        held.copy_(op)
+        return f(held, other, y=y) if what == "x" else f(other, held, y=y)
+
+    assert "k_conv_small" not in forward_kernels(run)
+    assert rel_err(to_f64(run()), ref) <= TOL["f32"]
+    free = buf[at + op.numel():at + op.numel() + 16 * n].view(n, 16)  # touches the operand's end
+    held.copy_(op)
+    a, b = (held, other) if what == "x" else (other, held)
+    assert forward_kernels(lambda: f(a, b, y=free)) == {"k_conv_small": 1}
+    assert rel_err(to_f64(free), ref) <= TOL["f32"]
 
 
 @pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 16, 128), ("f32", 16, 64)])

@@ -20,10 +20,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _cloud(seed, n, side):
-    rng = np.random.default_rng(seed)
-    cells = rng.choice(side ** 3, n, replace=False)
-    c = np.stack([np.zeros(n), cells // side ** 2, cells // side % side, cells % side], 1).astype(np.int32)
-    return np.ascontiguousarray(c)
+    return scenes.uniform_cells(n, side, seed)
 
 
 @pytest.mark.parametrize("dtype,K,c_in,c_out,n", [
