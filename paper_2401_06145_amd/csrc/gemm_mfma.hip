@@ -332,14 +332,18 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   // (they wait only for their rows), then the pieces go to LDS.  k past c_in is zero.
   const int m_first = r_begin + rg * MB * 16;
   fetch_rows(m_first);
-  if (wt) {
-    // from the transposed copy: 16-byte chunks, kWStage per thread in flight at a time
+  if constexpr (E == 8) {
+    // kWStage 16-byte chunks per thread in flight at a time: 8 consecutive k of one n from
+    // the transposed copy, or 8 consecutive n of one k from W itself, transposed on the way
+    // into LDS
     constexpr int CH_T = KP / E;  // chunks per W^T row
+    constexpr int CH_N = BN / E;  // chunks per W row slice
     constexpr int NCHUNK = BN * KP / E;
     constexpr int kWStage = 8;
-    const T* wk_t = wt + ((int64_t)k * c_out + n0) * c_in;
+    const T* wk_t = wt ? wt + ((int64_t)k * c_out + n0) * c_in : nullptr;
+    const T* wk_p = w + (int64_t)k * c_in * c_out + n0;
     uint4 wv[kWStage];
-    auto load_chunks = [&](int cb) {
+    auto load_t = [&](int cb) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < kWStage; ++u) {
         const int idx = cb + u * kWideThreads + tid;
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
                                            : make_uint4(0, 0, 0, 0);
       }
     };
-    auto store_chunks = [&](int cb) {
+    auto store_t = [&](int cb) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < kWStage; ++u) {
         const int idx = cb + u * kWideThreads + tid;
@@ -356,47 +360,68 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
         if (idx < NCHUNK) *reinterpret_cast<uint4*>(lw + n * ldk + c) = wv[u];
       }
     };
-    load_chunks(0);
-    issue(m_first);
-    store_chunks(0);
-    for (int cb = kWStage * kWideThreads; cb < NCHUNK; cb += kWStage * kWideThreads) {
-      load_chunks(cb);
-      store_chunks(cb);
-    }
-  } else if constexpr (E == 8) {
-    // from W itself, transposed on the way into LDS: a chunk is 8 consecutive n of one k
-    constexpr int CH_N = BN / 8;  // chunks per W row slice
-    constexpr int NCHUNK = KP * CH_N;
-    constexpr int kWStage = 8;
-    const T* wk_p = w + (int64_t)k * c_in * c_out + n0;
-    uint4 wv[kWStage];
-    auto load_chunks = [&](int cb) {
+    auto load_n = [&](int cb) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < kWStage; ++u) {
         const int idx = cb + u * kWideThreads + tid;
-        const int c = idx / CH_N, n = (idx - c * CH_N) * 8;
+        const int c = idx / CH_N, n = (idx - c * CH_N) * E;
         wv[u] = (idx < NCHUNK && c < c_in) ? *reinterpret_cast<const uint4*>(wk_p + (int64_t)c * c_out + n)
                                            : make_uint4(0, 0, 0, 0);
       }
     };
-    auto store_chunks = [&](int cb) {
+    auto store_n = [&](int cb) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < kWStage; ++u) {
         const int idx = cb + u * kWideThreads + tid;
-        const int c = idx / CH_N, n = (idx - c * CH_N) * 8;
+        const int c = idx / CH_N, n = (idx - c * CH_N) * E;
         const T* e = reinterpret_cast<const T*>(&wv[u]);
         if (idx < NCHUNK) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) lw[(n + j) * ldk + c] = e[j];
+          for (int j = 0; j < E; ++j) lw[(n + j) * ldk + c] = e[j];
         }
       }
     };
-    load_chunks(0);
-    issue(m_first);
-    store_chunks(0);
-    for (int cb = kWStage * kWideThreads; cb < NCHUNK; cb += kWStage * kWideThreads) {
-      load_chunks(cb);
-      store_chunks(cb);
+    constexpr int kStep = kWStage * kWideThreads;
+    if constexpr (KSTEPS < 16) {
+      if (wt) {
+        load_t(0);
+        issue(m_first);
+        store_t(0);
+        for (int cb = kStep; cb < NCHUNK; cb += kStep) {
+          load_t(cb);
+          store_t(cb);
+        }
+      } else {
+        load_n(0);
+        issue(m_first);
+        store_n(0);
+        for (int cb = kStep; cb < NCHUNK; cb += kStep) {
+          load_n(cb);
+          store_n(cb);
+        }
+      }
+    } else {
+      // one `issue` for both sources: with one each, the gathering instances spilled 8 to 40
+      // registers (512 -> 96 channels 44.3 -> 45.7 us); at fewer k-steps two are the faster
+      // (256 -> 512 by 3%)
+      if (wt)
+        load_t(0);
+      else
+        load_n(0);
+      issue(m_first);
+      if (wt)
+        store_t(0);
+      else
+        store_n(0);
+      for (int cb = kStep; cb < NCHUNK; cb += kStep) {
+        if (wt) {
+          load_t(cb);
+          store_t(cb);
+        } else {
+          load_n(cb);
+          store_n(cb);
+        }
+      }
     }
   } else {
     // float32, from W itself: 4 x 4 pieces, 16-byte accesses both ways
