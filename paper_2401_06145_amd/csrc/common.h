@@ -266,6 +266,7 @@ struct GemmSeg {
 // transposed beforehand (large W_k; small ones are transposed while staging).
 bool gemm_wide(int c_in, int c_out, int dtype, int part_dtype);
 bool gemm_wide_transposed(int c_in, int c_out, int dtype);
+bool gemm_general(int c_in, int dtype, int64_t rows);
 void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, int64_t cus, int64_t per_cu, int* nt,
                 int* rows);
 // wt[k][n][c] = w[k][c][n] for 16-bit weights.

@@ -999,12 +999,6 @@ int wide_nt(int c_in, int c_out, int elem) {
   if (c_in * elem % 16 != 0 || c_out % 16 != 0) return 0;
   const int ks = wide_ksteps(c_in, elem);
   if (ks == 0) return 0;
-  // float32 is bound by its products: the k-steps may hold at most a third more channels
-  // than the layer has, and no layer is narrower than one (k_gemm has steps of 4
-  // channels).  Times of k_gemm's, over 120 layers each: 4 channels 1.01 (2000 scattered
-  // voxels, K = 4, 4 -> 512: 23.9 against 12.8 us), 8 channels 0.99 with a fifth of them
-  // over 1.05; 12 and 20 channels 0.93 and 0.92, up to 1.19; 16 and 36 0.91 and 0.86.
-  if (elem == 4 && (c_in < 16 || 16 * ks * 3 > 4 * c_in)) return 0;
   const int nt_all = c_out / 16;
   for (int nt : {16, 12, 8, 6, 4, 3, 2, 1})
     if (nt_all % nt == 0 && wide_fits(nt, ks, elem)) return nt;
@@ -1138,6 +1132,13 @@ hipError_t gemm_t(const GemmLaunchArgs& g, int total_tiles, const void* A, const
 
 bool gemm_wide_transposed(int c_in, int c_out, int dtype) { return dtype != 0 && c_in * c_out >= 128 * 128; }
 
+// k_gemm for launches of `rows` rows that k_gemm_wide could take: float32 is bound by its
+// products, and k_gemm has k-steps of 4 channels where k_gemm_wide pads 4 or 8 to 16; its
+// whole-row stores outweigh that from 2^18 rows.  Times of k_gemm's: 4 channels 1.03 over 100
+// layers of fewer rows (8001 scattered voxels, K = 5, 4 -> 192 1.29), 0.88 over 22 of more; 8
+// channels 1.01 over 92, up to 1.25, and 0.84 over 18; 12 and 20 channels 0.93 and 0.92.
+bool gemm_general(int c_in, int dtype, int64_t rows) { return dtype == 0 && c_in < 12 && rows < (1 << 18); }
+
 bool gemm_wide(int c_in, int c_out, int dtype, int part_dtype) {
   // built for partials of the operands' type or of float32
   const bool pair = part_dtype == dtype || part_dtype == 0;
@@ -1238,7 +1239,10 @@ hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const
                        const void* wt, void* buf_out, void* dump_row, int c_in, int c_out, int dtype, int part_dtype,
                        int tile_rows, bool stream, hipStream_t s) {
   if (c_out % 16 != 0) return hipErrorInvalidValue;
-  const bool wide = dump_row && gemm_wide(c_in, c_out, dtype, part_dtype);
+  int64_t rows_all = 0;
+  for (int i = 0; i < n_seg; ++i) rows_all += segs[i].height;
+  const bool wide =
+      dump_row && gemm_wide(c_in, c_out, dtype, part_dtype) && !gemm_general(c_in, dtype, rows_all);
   int rows_per_tile = 64;
   const void* wfn = nullptr;
   int nt = 0, ks = 0, ldk = 0;
@@ -1268,8 +1272,6 @@ hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const
     rows_per_tile = (tile_rows + 15) / 16 * 16;
   } else {
     // enough workgroups to fill 256 CUs several times, at most 1024 rows each
-    int64_t rows_all = 0;
-    for (int i = 0; i < n_seg; ++i) rows_all += segs[i].height;
     while (rows_per_tile < 1024 && rows_all / (rows_per_tile * 2) >= 2048) rows_per_tile *= 2;
   }
   for (int base = 0; base < n_seg; base += kMaxSegPerLaunch) {

@@ -58,15 +58,15 @@ def test_float32_tiles_follow_the_work(heights, c_in, c_out, rows):
     assert _wide_tiles(heights, c_in, c_out, 4)[1] == rows
 
 
-@pytest.mark.parametrize("c_in,wide", [(4, False), (8, False), (12, False), (16, True), (20, False), (24, True),
-                                       (36, True), (64, True), (68, False), (72, True), (132, False), (144, True),
-                                       (256, True), (260, False)])
-def test_float32_full_width_pads_a_third_at_most(c_in, wide):
-    """k-steps of 16 channels (1, 2, 3, 4, 6, 8, 12 or 16 of them): layers that would pad more
-    than a third, or fill less than one step, keep the general product."""
-    gemm_wide = B.lib()._ZN3spc9gemm_wideEiiii
-    gemm_wide.restype = ctypes.c_bool
-    assert gemm_wide(c_in, 64, B.SPCONV_F32, B.SPCONV_F32) == wide
+@pytest.mark.parametrize("c_in,dtype,rows,general", [
+    (4, "F32", 2 ** 18 - 1, True), (4, "F32", 2 ** 18, False), (8, "F32", 1, True), (8, "F32", 10 ** 6, False),
+    (12, "F32", 1, False), (256, "F32", 1, False), (8, "F16", 1, False), (8, "BF16", 1, False),
+])
+def test_narrowest_float32_inputs_take_the_general_product(c_in, dtype, rows, general):
+    """Less than a k-step of the full-width product, unless there are many rows."""
+    f = B.lib()._ZN3spc12gemm_generalEiil
+    f.restype = ctypes.c_bool
+    assert f(c_in, getattr(B, "SPCONV_" + dtype), ctypes.c_int64(rows)) == general
 
 
 F32, F16, BF16 = B.SPCONV_F32, B.SPCONV_F16, B.SPCONV_BF16
