@@ -30,8 +30,8 @@
 // slice per workgroup.  float32 is bound by the rows it moves up to about 96 channels
 // and by v_mfma_f32_16x16x4_f32 from 128 on; its loads of 4 channels per lane and k-step
 // in k_gemm made four times the load instructions.  Layers through k_gemm and
-// k_gemm_wide: 120k LiDAR 64 -> 64, 92 -> 70 us; 256 -> 256, 1526 -> 567 us; 100k indoor
-// 128 -> 128, 306 -> 171 us; 37k LiDAR level-1 128 -> 256, 412 -> 217 us.
+// k_gemm_wide: 120k LiDAR 64 -> 64, 94 -> 70 us; 256 -> 256, 1523 -> 570 us; 100k indoor
+// 128 -> 128, 315 -> 171 us; 37k LiDAR level-1 128 -> 256, 411 -> 221 us.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -1196,17 +1196,19 @@ hipError_t wide_occupancy(const void* fn, size_t lds, int* per_cu, int* cus, int
 void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, int64_t cus, int64_t per_cu, int* nt,
                 int* rows) {
   *nt = wide_nt(c_in, c_out, elem);
-  const int round = wide_round_rows(*nt, wide_ksteps(c_in, elem), elem);
+  const int ks = wide_ksteps(c_in, elem);
+  const int round = wide_round_rows(*nt, ks, elem);
   int64_t all = 0;
   for (int i = 0; i < n_seg; ++i) all += segs[i].height;
   auto set_rows = [&](int64_t r) {
     *rows = (int)(std::min<int64_t>(std::max<int64_t>((r + round - 1) / round, 1), 16) * round);
   };
-  auto workgroups = [&] {
+  auto tiles = [&] {
     int64_t t = 0;
     for (int i = 0; i < n_seg; ++i) t += (segs[i].height + *rows - 1) / *rows;
-    return t * (c_out / 16 / *nt);
+    return t;
   };
+  auto workgroups = [&] { return tiles() * (c_out / 16 / *nt); };
   // about two tiles per workgroup slot: larger tiles amortise the W^T staging, and
   // two rounds of them keep the last round's idle CUs few; at least 512 rows (smaller
   // tiles measured slower: C = 256 GEMM 155 -> 150 us, 120k LiDAR layer 16.4 -> 15.5 us)
@@ -1223,13 +1225,18 @@ void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, i
   // column slices (they read their rows again, from the L2).  Layer times, f16
   // unless noted: 128 -> 256 stride 2, 113 tiles: 256 rows 30.4 -> 26.1 us; 256 -> 128
   // transposed, 121 tiles: 29.5 -> 25.0 us; 636 voxels 256 -> 256, 27 tiles: 128 rows
-  // 49.9 -> 37.3, slices of a quarter 33.4 us; 3000 scattered voxels 64 -> 128 float32:
-  // slices of a quarter 18.5 -> 11.6 us.  From the line up both lose: 128 -> 128 with
-  // 240 tiles, 256 rows 34.6 -> 36.4, half slices 38.2 us; at exactly half, half slices of
-  // 128 rows: 384 -> 256 stride 2 34.2 -> 39.8 us, 512 -> 192, K = 1, 39.2 -> 44.9 us.
+  // 49.9 -> 37.3, slices of a quarter 33.4 us.  Above the line both lose: 128 -> 128 with
+  // 240 tiles, 256 rows 34.6 -> 36.4, half slices 38.2 us.  At exactly half (powers of two
+  // meet it often) half slices of 128 rows lose where tiles are long and a slice's weights
+  // take long to stage, and win otherwise: 384 -> 256 stride 2 34.2 -> 39.8 us, 512 -> 192,
+  // K = 1, 39.2 -> 44.9; 32 -> 384 transposed 27.9 -> 25.2, 2000 voxels, K = 5, 384 -> 128
+  // 49.3 -> 36.0.
   for (int r = 256; r >= 128 && 2 * workgroups() < cus; r /= 2)
     if (r < *rows) set_rows(r);
-  while (*nt % 2 == 0 && 2 * workgroups() < cus) {
+  const auto idle = [&] {
+    return 2 * workgroups() < cus || (2 * workgroups() == cus && (ks <= 4 || all <= 256 * tiles()));
+  };
+  while (*nt % 2 == 0 && idle()) {
     *nt /= 2;
     set_rows(128);
   }

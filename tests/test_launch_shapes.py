@@ -28,13 +28,16 @@ def _wide_tiles(heights, c_in, c_out, elem, per_cu=1):
 
 
 @pytest.mark.parametrize("heights,c_in,c_out,nt,rows", [
-    ([4096] * 8, 384, 256, 8, 512),     # K = 2 stride 2, two slices: 128 workgroups
-    ([32768], 512, 192, 6, 512),        # K = 1, two slices: 128 workgroups
-    ([512] * 128, 32, 64, 4, 512),      # one slice
+    ([4096] * 8, 384, 256, 8, 512),           # K = 2 stride 2, two slices: 128 workgroups
+    ([32768], 512, 192, 6, 512),              # K = 1, two slices: 128 workgroups
+    ([512] * 128, 160, 64, 4, 512),           # one slice
+    ([512] * 128, 64, 64, 2, 128),            # the same with fewer weights: half slices
+    ([2000] + [15] * 124, 384, 128, 4, 128),  # 128 workgroups, most of few rows
 ])
-def test_half_the_card_keeps_its_tiles(heights, c_in, c_out, nt, rows):
-    """Exactly half the CUs with a workgroup: tiles stay at 512 rows and the full slice."""
-    assert _wide_tiles(heights, c_in, c_out, 2) == (nt, rows, CUS // 2)
+def test_exactly_half_the_card(heights, c_in, c_out, nt, rows):
+    """Exactly half the CUs with a workgroup: long tiles with many weights stay at 512 rows
+    and the full slice, others take half slices."""
+    assert _wide_tiles(heights, c_in, c_out, 2)[:2] == (nt, rows)
 
 
 def test_fewer_workgroups_shrink_tiles_then_slices():
