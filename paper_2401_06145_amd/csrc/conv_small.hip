@@ -11,17 +11,17 @@
 //
 // What bounds it: the latency of a block's chain (table entries -> pairs' input rows ->
 // input rows -> products -> store) over the 16 waves a CU holds beside the weights; the
-// chain's first links are requested one and two blocks ahead.  Measured against the
+// chain's first links are requested one and two blocks ahead.  Layer times against the
 // separate GEMM and scatter (one launch instead of two): K = 5, 8 -> 32 channels, 60k
-// voxels 38.5 -> 19.4 us; K = 3, 32 -> 32, 242k voxels 34.0 -> 23.2 us (its table, rows
-// and outputs are 60 MB: 2.6 TB/s); K = 2 stride 2, 32 -> 64, 199k voxels 22.9 -> 13.1
-// us, transposed 64 -> 32 19.7 -> 13.9 us, 96 -> 96 41.0 -> 23.5 us.
+// voxels 38.6 -> 18.6 us; K = 3, 32 -> 32, 242k voxels 33.8 -> 23.7 us (its table, rows
+// and outputs are 60 MB: 2.5 TB/s); K = 2 stride 2, 32 -> 64, 199k voxels 22.4 -> 13.6
+// us, transposed 64 -> 32 18.9 -> 14.6 us, 96 -> 96 36.2 -> 21.4 us.
 //
-// Tried and slower: float32 sums in LDS (ds_add_f32 took 5 cycles a lane; read, add and
-// write by one wave 1.3 times the separate steps' time); the weights of wider layers
-// streamed through LDS offset by offset (a barrier per offset: 2 to 4 times), or a few
-// offsets at a time with two row blocks per wave (even at 64 and 128 channels, twice
-// the time at 256).
+// Tried and slower, as far as the trials were kept: float32 sums in LDS (ds_add_f32, or
+// read, add and write by one wave), and wider layers with their weights streamed through
+// LDS, offset by offset with a barrier each, or a few offsets at a time with two row
+// blocks per wave (about even with the separate steps at 64 and 128 channels, behind them
+// at 256).
 #include <algorithm>
 #include <type_traits>
 
@@ -453,8 +453,8 @@ __global__ __launch_bounds__(kConvThreads) void k_conv_small(ConvArgs g) {
               // a step's sum by itself: one chain over all offsets' channels rounds more.
               // Error against 64 bits, one chain -> this, and time: 60k LiDAR 32 -> 32 2.4e-7
               // -> 1.1e-7, 19.1 -> 18.9 us; 16 -> 64 1.7e-7 -> 0.9e-7, 19.5 -> 20.2 us; K = 5
-              // 8 -> 32 2.0e-7 -> 0.9e-7, 30.1 -> 31.0 us (the separate steps: 1.1e-7 and 34.6
-              // us, 0.9e-7 and 36.5 us, 0.9e-7 and 47.2 us).
+              // 8 -> 32 2.0e-7 -> 0.9e-7, 30.1 -> 31.0 us (the separate steps: 1.1e-7 and 25.2
+              // us, 0.9e-7 and 31.6 us, 0.9e-7 and 47.8 us).
 #pragma unroll
               for (int t = 0; t < NT; ++t) {
                 f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
