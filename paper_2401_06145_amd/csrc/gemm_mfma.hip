@@ -214,10 +214,13 @@ constexpr size_t wide_lds(int nt, int ks) { return (size_t)16 * nt * (64 * ks + 
 // operands alone take 128 registers there).  Measured on gfx950: C = 128 GEMM 0.142 -> 0.132 ms; at C = 64
 // one block per wave is faster (26.5 vs 28.5 us on the 120k LiDAR layer), at
 // C = 32 the two are equal; one block per wave stays faster in one chunk; CG > 1
-// cost more occupancy than it saved.  float32 stays at one block: its products take four
-// times as long per fragment read, and with two a tile has 256 rows at the least.
+// cost more occupancy than it saved.  float32 takes two blocks where a tile has 512 rows or more
+// (120k LiDAR 64 -> 64, inputs from memory: 77.3 -> 74.1 us) and one, in tiles of whole 128 rows,
+// in smaller launches (1728 voxels, 64 -> 48: 11.1 -> 9.9 us).
 constexpr int wide_cg(int) { return 1; }
-constexpr int wide_mb(int elem, int ksteps) { return (elem == 2 && (ksteps == 3 || ksteps == 4)) ? 2 : 1; }
+constexpr int wide_mb(int elem, int ksteps, int rows) {
+  return (ksteps == 3 || ksteps == 4) && (elem == 2 || rows >= 512) ? 2 : 1;
+}
 constexpr int wide_nch(int ntw, int mb, int ksteps) {
   int nch = 1;
   while ((mb > 1 || ksteps >= 16) && ntw / nch > (mb > 1 ? 8 : 2) && ntw % (2 * nch) == 0) nch *= 2;
@@ -232,7 +235,7 @@ constexpr int wide_nch(int ntw, int mb, int ksteps) {
 // valid dummy address; k past c_in is then zeroed, rows past the segment compute
 // values that only reach the dump row.  So the compiler keeps the next blocks'
 // loads in flight across the current blocks' MFMAs.
-template <typename T, typename TO, int NT, int KSTEPS, bool GATHER>
+template <typename T, typename TO, int NT, int KSTEPS, bool GATHER, int MB>
 __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, const T* __restrict__ A,
                                                             const int32_t* __restrict__ arows,
                                                             const T* __restrict__ w, const T* __restrict__ wt,
@@ -246,7 +249,6 @@ __global__ __launch_bounds__(kWideThreads) void k_gemm_wide(GemmLaunchArgs g, co
   static_assert(E * sizeof(T) == 16 && KS == 4 * E, "16-byte fragments");
   constexpr int CG = wide_cg(NT);
   constexpr int NTW = NT / CG;
-  constexpr int MB = wide_mb((int)sizeof(T), KSTEPS);
   constexpr int NCH = wide_nch(NTW, MB, KSTEPS);
   constexpr int NTC = NTW / NCH;  // column tiles per chunk
   static_assert(NTW % NCH == 0, "chunks must split the tiles");
@@ -1005,35 +1007,44 @@ int wide_nt(int c_in, int c_out, int elem) {
   return 0;
 }
 
-// Rows of one round of the workgroup (tiles are whole rounds).
-int wide_round_rows(int nt, int ks, int elem) { return kWideWaves / wide_cg(nt) * wide_mb(elem, ks) * 16; }
+// Rows of one round of the workgroup (tiles are whole rounds) in tiles of about `rows` rows.
+int wide_round_rows(int nt, int ks, int elem, int64_t rows) {
+  return kWideWaves / wide_cg(nt) * wide_mb(elem, ks, rows < 512 ? 0 : 512) * 16;
+}
 
 template <typename T, typename TO, bool GATHER>
-const void* wide_kernel(int nt, int ks) {
-#define SPC_W(N, KS_)                                                                                     \
-  if constexpr (wide_fits(N, KS_, (int)sizeof(T))) {                                                                       \
-    if (nt == N && ks == KS_) return reinterpret_cast<const void*>(&k_gemm_wide<T, TO, N, KS_, GATHER>); \
-  }
+const void* wide_kernel(int nt, int ks, int rows) {
+  const int mb = wide_mb((int)sizeof(T), ks, rows);
+#define SPC_WM(N, KS_, MB_)                               \
+  if constexpr (wide_fits(N, KS_, (int)sizeof(T)))        \
+    if (nt == N && ks == KS_ && mb == MB_)                \
+      return reinterpret_cast<const void*>(&k_gemm_wide<T, TO, N, KS_, GATHER, MB_>);
+#define SPC_W(N, KS_) SPC_WM(N, KS_, 1)
+#define SPC_W2(N, KS_)                               \
+  SPC_WM(N, KS_, 2)                                  \
+  if constexpr (sizeof(T) == 4) { SPC_WM(N, KS_, 1) }
 #define SPC_WK(N) \
-  SPC_W(N, 1) SPC_W(N, 2) SPC_W(N, 3) SPC_W(N, 4) SPC_W(N, 6) SPC_W(N, 8) SPC_W(N, 12) SPC_W(N, 16)
+  SPC_W(N, 1) SPC_W(N, 2) SPC_W2(N, 3) SPC_W2(N, 4) SPC_W(N, 6) SPC_W(N, 8) SPC_W(N, 12) SPC_W(N, 16)
   SPC_WK(1) SPC_WK(2) SPC_WK(3) SPC_WK(4) SPC_WK(6) SPC_WK(8) SPC_WK(12) SPC_WK(16)
 #undef SPC_WK
+#undef SPC_W2
 #undef SPC_W
+#undef SPC_WM
   return nullptr;
 }
 
-const void* wide_kernel_for(int dtype, int part_dtype, bool gather, int nt, int ks) {
+const void* wide_kernel_for(int dtype, int part_dtype, bool gather, int nt, int ks, int rows) {
   if (dtype == 0 && part_dtype == 0)
-    return gather ? wide_kernel<float, float, true>(nt, ks) : wide_kernel<float, float, false>(nt, ks);
+    return gather ? wide_kernel<float, float, true>(nt, ks, rows) : wide_kernel<float, float, false>(nt, ks, rows);
   if (dtype == 1 && part_dtype == 0)
-    return gather ? wide_kernel<__half, float, true>(nt, ks) : wide_kernel<__half, float, false>(nt, ks);
+    return gather ? wide_kernel<__half, float, true>(nt, ks, rows) : wide_kernel<__half, float, false>(nt, ks, rows);
   if (dtype == 1 && part_dtype == 1)
-    return gather ? wide_kernel<__half, __half, true>(nt, ks) : wide_kernel<__half, __half, false>(nt, ks);
+    return gather ? wide_kernel<__half, __half, true>(nt, ks, rows) : wide_kernel<__half, __half, false>(nt, ks, rows);
   if (dtype == 2 && part_dtype == 2)
-    return gather ? wide_kernel<__hip_bfloat16, __hip_bfloat16, true>(nt, ks)
-                  : wide_kernel<__hip_bfloat16, __hip_bfloat16, false>(nt, ks);
+    return gather ? wide_kernel<__hip_bfloat16, __hip_bfloat16, true>(nt, ks, rows)
+                  : wide_kernel<__hip_bfloat16, __hip_bfloat16, false>(nt, ks, rows);
   if (dtype == 2 && part_dtype == 0)
-    return gather ? wide_kernel<__hip_bfloat16, float, true>(nt, ks) : wide_kernel<__hip_bfloat16, float, false>(nt, ks);
+    return gather ? wide_kernel<__hip_bfloat16, float, true>(nt, ks, rows) : wide_kernel<__hip_bfloat16, float, false>(nt, ks, rows);
   return nullptr;
 }
 
@@ -1197,10 +1208,10 @@ void wide_tiles(const GemmSeg* segs, int n_seg, int c_in, int c_out, int elem, i
                 int* rows) {
   *nt = wide_nt(c_in, c_out, elem);
   const int ks = wide_ksteps(c_in, elem);
-  const int round = wide_round_rows(*nt, ks, elem);
   int64_t all = 0;
   for (int i = 0; i < n_seg; ++i) all += segs[i].height;
   auto set_rows = [&](int64_t r) {
+    const int round = wide_round_rows(*nt, ks, elem, r);
     *rows = (int)(std::min<int64_t>(std::max<int64_t>((r + round - 1) / round, 1), 16) * round);
   };
   auto tiles = [&] {
@@ -1261,16 +1272,18 @@ hipError_t launch_gemm(const GemmSeg* segs, int n_seg, const void* buf_in, const
     ldk = (64 * ks + 16) / elem;
     auto instance = [&] {
       lds = wide_lds(nt, ks);
-      wfn = wide_kernel_for(dtype, part_dtype, a_rows != nullptr, nt, ks);
+      wfn = wide_kernel_for(dtype, part_dtype, a_rows != nullptr, nt, ks, rows_per_tile);
       return wfn ? hipSuccess : hipErrorInvalidValue;
     };
-    hipError_t e = instance();
-    if (e != hipSuccess) return e;
+    hipError_t e;
     if (tile_rows > 0) {
-      const int round = wide_round_rows(nt, ks, elem);
+      const int round = wide_round_rows(nt, ks, elem, tile_rows);
       rows_per_tile = (tile_rows + round - 1) / round * round;
+      if ((e = instance()) != hipSuccess) return e;
     } else {
       int per_cu = 0, cus = 0;
+      rows_per_tile = 512;  // the instance of large launches
+      if ((e = instance()) != hipSuccess) return e;
       if ((e = wide_occupancy(wfn, lds, &per_cu, &cus)) != hipSuccess) return e;
       wide_tiles(segs, n_seg, c_in, c_out, elem, std::max(cus, 1), std::max(per_cu, 1), &nt, &rows_per_tile);
       if ((e = instance()) != hipSuccess) return e;

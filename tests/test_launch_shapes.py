@@ -53,11 +53,15 @@ def test_fewer_workgroups_shrink_tiles_then_slices():
     ([3000] * 8, 64, 64, 128),                # 94 rows for each CU
     ([20000] * 4, 64, 64, 384),               # 312 rows for each CU
     ([20000] * 4, 64, 512, 512),
-    ([120000] + [8000] * 26, 64, 64, 768),    # 641 rows for each of two rounds of tiles
+    ([120000] + [8000] * 26, 64, 64, 768),    # 641 rows for each of two rounds of tiles: two row blocks
+    ([120000] + [8000] * 26, 128, 64, 768),   # (one)
+    ([200000] + [8000] * 26, 64, 64, 1024),   # 797 rows
+    ([200000] + [8000] * 26, 128, 64, 896),
 ])
 def test_float32_tiles_follow_the_work(heights, c_in, c_out, rows):
     """float32 tiles hold one CU's share of the rows times column slices, 128 to 512 rows
-    (whole rounds of 128), before the rule for large launches."""
+    (whole rounds of 128; of 256 from 512 rows at 33 to 64 channels, where a wave takes two row
+    blocks), before the rule for large launches."""
     assert _wide_tiles(heights, c_in, c_out, 4)[1] == rows
 
 
