@@ -556,10 +556,15 @@ ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, 
 
 }  // namespace
 
+namespace {
+// (positions up to two rounds of blocks past the last output are held in 32 bits)
+bool conv_rows_fit(int64_t n_in, int64_t n_out, int c_in, int dtype) {
+  return n_out < ((int64_t)1 << 31) - (1 << 16) && n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes;
+}
+}  // namespace
+
 bool conv_small_applies(int64_t n_in, int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
-  // (positions up to two rounds of blocks past the last output are held in 32 bits)
-  return n_out < ((int64_t)1 << 31) - (1 << 16) && n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes &&
-         conv_shape(n_out, pairs, K3, c_in, c_out, dtype).fn;
+  return conv_rows_fit(n_in, n_out, c_in, dtype) && conv_shape(n_out, pairs, K3, c_in, c_out, dtype).fn;
 }
 
 hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const int32_t* pin, const int32_t* omt,
@@ -567,8 +572,8 @@ hipError_t launch_conv_small(const void* x, int64_t n_in, const void* w, const i
                              const void* residual, int relu, int64_t n_out, int c_in, int c_out, int dtype,
                              hipStream_t s) {
   if (n_out <= 0) return hipSuccess;
-  if (!conv_small_applies(n_in, n_out, pairs, K3, c_in, c_out, dtype)) return hipErrorInvalidValue;
   const ConvShape sh = conv_shape(n_out, pairs, K3, c_in, c_out, dtype);
+  if (!sh.fn || !conv_rows_fit(n_in, n_out, c_in, dtype)) return hipErrorInvalidValue;
   ProfScope ps(KN_CONV_SMALL, s);
   ConvArgs g;
   g.x = x;
