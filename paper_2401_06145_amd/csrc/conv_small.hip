@@ -554,13 +554,11 @@ ConvShape conv_shape(int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, 
   return conv_shape_k<__hip_bfloat16>(K3, nt, kpo, gr);
 }
 
-}  // namespace
-
-namespace {
 // (positions up to two rounds of blocks past the last output are held in 32 bits)
 bool conv_rows_fit(int64_t n_in, int64_t n_out, int c_in, int dtype) {
   return n_out < ((int64_t)1 << 31) - (1 << 16) && n_in * c_in * (dtype == 0 ? 4 : 2) <= kMaxInputBytes;
 }
+
 }  // namespace
 
 bool conv_small_applies(int64_t n_in, int64_t n_out, int64_t pairs, int K3, int c_in, int c_out, int dtype) {
