@@ -402,6 +402,11 @@ std::vector<int> dp_groups(const std::vector<int>& order, const std::vector<int6
 // Otherwise their dirty lines stay in the caches, and the next kernels' traffic has to
 // write them back.
 constexpr int64_t kStreamPartialBytes = (int64_t)128 << 20;
+// float32 partials, whose products give the caches more time per byte, stream from 256 MiB:
+// layers of 128 to 256 MiB, streamed, took up to 1.19 times k_gemm's time (112k voxels,
+// K = 2, 4 -> 192 111.7 us), stored plainly at most 1.05 (99.0), over 141 shapes 0.98 times the
+// streamed form's; of 256 to 384 MiB streamed ones 0.98 times the plain ones' over 67.
+constexpr int64_t kStreamPartialBytesF32 = (int64_t)256 << 20;
 constexpr int64_t kStreamOutputBytes = (int64_t)64 << 20;
 
 int make_plan(const spconv_map* m, int c_in, int c_out, int dtype, const spconv_options* opt, GmasPlan* p) {
@@ -1007,7 +1012,8 @@ int forward_impl(const spconv_map* m, const void* d_x, const void* d_w, void* d_
       // fused: the A rows are the input rows of the pairs (pair r reads x[pin[r]])
       const void* a_src = fused ? d_x : b.buf_in;
       const int32_t* a_rows = fused ? m->pin : nullptr;
-      const bool stream = (int64_t)p.rows_pairs * c_out * p.pelem >= kStreamPartialBytes;
+      const bool stream = (int64_t)p.rows_pairs * c_out * p.pelem >=
+                          (dtype == SPCONV_F32 ? kStreamPartialBytesF32 : kStreamPartialBytes);
       for (const auto& segs : p.launches)
         SPC_TRY(launch_gemm(segs.data(), (int)segs.size(), a_src, a_rows, d_w, b.wt, b.buf_out,
                             static_cast<char*>(b.buf_out) + (size_t)p.rows_pairs * c_out * p.pelem, c_in, c_out,
