@@ -590,7 +590,8 @@ def cpu_baseline(coords, x, w, L, rows_all=96000, rows_one=24000):
     threads = oracle.max_threads()
     xf, wf = scenes.to_f64(x, L.dtype), scenes.to_f64(w, L.dtype)
     t0 = time.perf_counter()
-    km = oracle.kernel_map(coords, None, L.K, 1, L.mode)
+    q = None if L.mode == "subm" else oracle.out_coords(coords, L.stride, 1)
+    km = oracle.kernel_map(coords, q, L.K, 1, L.mode)
     map_ms = (time.perf_counter() - t0) * 1e3
     n_out = km.n_out
     rng = np.random.default_rng(4242)

@@ -50,3 +50,13 @@ def test_weight_scale():
     w = scenes.weights(3, 64, 64, "f16", 1).astype(np.float64)
     assert w.shape == (27, 64, 64)
     assert abs(w.std() - 1 / np.sqrt(27 * 64)) < 0.05 / np.sqrt(27 * 64)
+
+
+def test_bench_cpu_baseline_of_a_strided_layer():
+    """The oracle's side of the layer benchmark needs the output coordinates of a strided layer."""
+    import bench
+
+    L = scenes.workload(2).layers[0]
+    coords = scenes.uniform_cells(300, 12, 5)
+    x, w = scenes.features(300, L.c_in, L.dtype, 1), scenes.weights(L.K, L.c_in, L.c_out, L.dtype, 2)
+    assert bench.cpu_baseline(coords, x, w, L)["value"] > 0
